@@ -686,12 +686,14 @@ int grow_lists(ljmd_ctx *c, int32_t need) {
 // error is returned.
 int check_overflow(ljmd_ctx *c, Ctl *h, bool *redo) {
     *redo = false;
-    hipError_t e = launch_max_fill(launcher(c));
-    if (e != hipSuccess) return hip_fail(c, e, "max_fill");
     int r = read_ctl(c, h);
     if (r) return r;
     if (h->flags == 0u) return LJMD_OK;
     if (h->flags != kErrList) return flags_status(c, h->flags);
+    // The longest list is only needed (and only counted) after an overflow.
+    hipError_t e = launch_max_fill(launcher(c));
+    if (e != hipSuccess) return hip_fail(c, e, "max_fill");
+    if ((r = read_ctl(c, h))) return r;
     if ((r = grow_lists(c, h->max_fill))) return r;
     *redo = true;
     return LJMD_OK;
