@@ -168,9 +168,6 @@ __host__ __device__ inline int64_t nbr_index(int64_t i, int32_t k, int32_t lanes
     return ((chunk * (int64_t)cap) << pg) + ((int64_t)(m >> 2) << 8) + (L << 2) + (m & 3);
 }
 
-// Entry m of the lane whose entries start at nbl (its chunk's base + 4*L).
-__device__ inline int32_t nb_entry(const int32_t *nbl, int m) { return nbl[((int64_t)(m >> 2) << 8) + (m & 3)]; }
-
 // List capacity granule: whole groups of four entries per lane.
 __host__ __device__ inline int32_t cap_granule(int32_t lanes) { return 4 * lanes > 16 ? 4 * lanes : 16; }
 
