@@ -286,8 +286,9 @@ __global__ __launch_bounds__(kBlock) void k_batch_obs(State st, Geom g, const Sy
     __shared__ double red[kBlock][6];
     const SysC &y = sys[blockIdx.x];
     double acc[6] = {0, 0, 0, 0, 0, 0};
-    for (int b = threadIdx.x; b < y.nb; b += kBlock) {
-        const double *r = st.partials + ((size_t)slot * g.max_blocks + y.b_off + b) * kNP;
+    constexpr int rows = kBlock / kRowThreads;  // rows of partials per block of the step kernel
+    for (int b = threadIdx.x; b < y.nb * rows; b += kBlock) {
+        const double *r = st.partials + ((size_t)slot * g.max_blocks + (size_t)y.b_off * rows + b) * kNP;
         for (int q = 0; q < 6; ++q) acc[q] += r[q];
     }
     for (int q = 0; q < 6; ++q) red[threadIdx.x][q] = acc[q];

@@ -21,6 +21,10 @@
 
 namespace ljmd {
 
+// Word 3 of a buffer descriptor: raw bytes (32-bit data format), so that an
+// access past num_records reads 0.
+constexpr int kRawBuffer = 0x00027000;
+
 // Housekeeping shared by both precisions: the rebuilt marker of this step and,
 // after a rebuild, clearing the cell counters for the next binning.
 // Cells [c_lo, c_hi) belong to this system; block bj of its nbj blocks
@@ -58,31 +62,97 @@ __device__ inline void step_housekeeping(const StepArgs &a, const Ctl *ctl, int6
 // TH: the thermostat resamples colliding particles' velocities after
 // "finalize" (a separate instantiation, so that the plain NVE kernel keeps
 // its register budget).
-template <int NS, int LANES, bool Q, bool OBS, bool TH = false, bool PLAIN = false>
+// BS: threads per block. SMALL: the form for boxes that leave the chip's wave
+// slots mostly empty (see the pair loop).
+template <int NS, int LANES, bool Q, bool OBS, bool TH = false, bool PLAIN = false, int BS = kBlock,
+          bool SMALL = false>
 __device__ inline void step_ds_body(const StepArgs &a, const BoxC &box, Ctl *ctl, int blk, int64_t i_end,
                                     int64_t c_lo, int64_t c_hi, int bj, int nbj, int32_t *rebuilt) {
     constexpr int P = kWave / LANES;
-    constexpr int WPB = kBlock / kWave;
+    constexpr int WPB = BS / kWave;
     const State &st = a.st;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int64_t chunk = (int64_t)blk * WPB + wv;
     const int l = lane % LANES;
     const int64_t i = chunk * P + lane / LANES;
     const bool valid = i < i_end;
+    // SMALL: loads through buffer descriptors, which the compiler keeps where
+    // they are written (it sinks plain loads of read-only memory to their
+    // first use, past scheduling barriers). Everything the wave reads outside
+    // its trips is asked for at once, ahead of the halt check: own record,
+    // list length, first list entries, and the step tail's operands.
+    constexpr int UQ = 8;  // list entries of a lane per trip
+    const int4 *__restrict__ rec = st.recq[a.cur];
+    [[maybe_unused]] __amdgpu_buffer_rsrc_t rsrc_rec, rsrc_nb;
+    int4 ri = make_int4(0, 0, 0, 0);
+    int cnt = 0;
+    [[maybe_unused]] int jn[UQ];
+    [[maybe_unused]] int4 xr;
+    [[maybe_unused]] DsState ds;
+    // Two 16-byte group loads: entries m .. m + 7 of the lane.
+    const int32_t *__restrict__ nb = st.nbr + chunk * (int64_t)(P * a.g.cap) + 4 * lane;
+    auto entries = [&](int m, int (&jj)[UQ]) {
+        if constexpr (SMALL) {
+            const auto g0 = __builtin_amdgcn_raw_buffer_load_b128(rsrc_nb, lane << 4, m << 8, 0);
+            const auto g1 = __builtin_amdgcn_raw_buffer_load_b128(rsrc_nb, (lane << 4) + 1024, m << 8, 0);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) jj[u] = (int)g0[u], jj[4 + u] = (int)g1[u];
+        } else {
+            const int4 g0 = *reinterpret_cast<const int4 *>(nb + ((int64_t)(m >> 2) << 8));
+            const int4 g1 = *reinterpret_cast<const int4 *>(nb + ((int64_t)((m >> 2) + 1) << 8));
+            jj[0] = g0.x, jj[1] = g0.y, jj[2] = g0.z, jj[3] = g0.w;
+            jj[4] = g1.x, jj[5] = g1.y, jj[6] = g1.z, jj[7] = g1.w;
+        }
+    };
+    if constexpr (SMALL) {
+        // Slots past the last particle read 0 (out of the descriptor's range).
+        auto rsrc = [](const void *p, int64_t bytes) {
+            return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, kRawBuffer);
+        };
+        const int64_t wchunk = __builtin_amdgcn_readfirstlane((int)chunk);
+        rsrc_rec = rsrc(rec, a.g.n << 4);
+        rsrc_nb = rsrc(st.nbr + wchunk * (P * a.g.cap), wchunk * P < a.g.n ? P * a.g.cap * 4 + kListPad * 4 : 0);
+        const __amdgpu_buffer_rsrc_t rsrc_cnt = rsrc(st.nbr_cnt, a.g.n << 2), rsrc_xr = rsrc(st.xref, a.g.n << 4);
+        const int o16 = (int)i << 4;
+        const uint32_t c = __builtin_amdgcn_raw_buffer_load_b32(rsrc_cnt, (int)i << 2, 0, 0);
+        const auto r = __builtin_amdgcn_raw_buffer_load_b128(rsrc_rec, o16, 0, 0);
+        entries(0, jn);
+        const auto x = __builtin_amdgcn_raw_buffer_load_b128(rsrc_xr, o16, 0, 0);
+        float4 w[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const auto v = __builtin_amdgcn_raw_buffer_load_b128(rsrc(st.dsw[k], a.g.n << 4), o16, 0, 0);
+            w[k] = make_float4(__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2]), __uint_as_float(v[3]));
+        }
+        // One word of every 64-byte line of the kernel arguments, so that the
+        // constants of the step tail come from the scalar cache later on.
+        const auto *arg = (const __attribute__((address_space(4))) int *)__builtin_amdgcn_kernarg_segment_ptr();
+        constexpr int kArgLines = (int)((sizeof(StepArgs) + 63) / 64);
+        int touch = 0;
+#pragma unroll
+        for (int k = 0; k < kArgLines; ++k) touch |= arg[k * 16];
+        asm volatile("" ::"s"(touch));
+        __builtin_amdgcn_sched_barrier(0);
+        ri = make_int4((int)r[0], (int)r[1], (int)r[2], (int)r[3]);
+        xr = make_int4((int)x[0], (int)x[1], (int)x[2], (int)x[3]);
+        ds = ds_unpack(w[0], w[1], w[2]);
+        cnt = valid ? (int)c : 0;
+    }
     if (halted_record(ctl, a.step, bj == 0)) return;
     step_housekeeping(a, ctl, c_lo, c_hi, bj, nbj, rebuilt);
-
-    // Own record (position and species). The double-single state and the
-    // list reference are read once, by the step tail after the pair loop:
-    // reading the state here as well and again there costs a second fetch,
-    // because the list stream of the loop evicts it from L2. (Staging the
-    // tail's operands in LDS with asynchronous loads issued here measured
-    // 0.7 us slower per launch at N = 256,000.)
-    const int4 *__restrict__ rec = st.recq[a.cur];
-    const int4 ri = valid ? rec[i] : make_int4(0, 0, 0, 0);
-    int cnt = valid ? st.nbr_cnt[i] : 0;
+    // Own record (position and species). In the form for large boxes the
+    // double-single state and the list reference are read by the step tail
+    // after the pair loop: reading the state here as well and again there
+    // costs a second fetch, because the list stream of the loop evicts it from
+    // L2. (Staging the tail's operands in LDS with asynchronous loads issued
+    // here measured 0.7 us slower per launch at N = 256,000.)
+    if constexpr (!SMALL) {
+        if (valid) {
+            ri = rec[i];
+            cnt = st.nbr_cnt[i];
+        }
+    }
     cnt = cnt < a.g.cap ? cnt : a.g.cap;
-    const int32_t *__restrict__ nb = st.nbr + chunk * (int64_t)(P * a.g.cap) + 4 * lane;
     const int iters = cnt > l ? (cnt - l + LANES - 1) / LANES : 0;
     const float qsx = box.qs_hi[0], qsy = box.qs_hi[1], qsz = box.qs_hi[2];
     const float qlx = box.qs_lo[0], qly = box.qs_lo[1], qlz = box.qs_lo[2];
@@ -111,20 +181,29 @@ __device__ inline void step_ds_body(const StepArgs &a, const BoxC &box, Ctl *ctl
         // Per lane over a few dozen pairs, in FP32: one species, sum s6^2 and
         // sum s6; two species, the pair energies and virials themselves.
         float sa = 0.f, sb = 0.f;
-        // Eight entries per trip (two 16-byte group loads per lane) keep more
-        // of the list stream in flight; groups past a list end read padding
-        // or other lists (valid indices) and are skipped. (Masking the loads
-        // of entries past a lane's list end instead, per entry, serialised
-        // them: 38.5 us against 30.3 us per launch at N = 256,000.)
-        constexpr int UQ = 8;
         static_assert((size_t)4 * kWave <= kListPad, "list padding below the unroll depth");
-        for (int m = 0; m < iters; m += UQ) {
-            const int4 g0 = *reinterpret_cast<const int4 *>(nb + ((int64_t)(m >> 2) << 8));
-            const int4 g1 = *reinterpret_cast<const int4 *>(nb + ((int64_t)((m >> 2) + 1) << 8));
-            const int jj[UQ] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
-            int4 rr[UQ];
+        auto gather = [&](const int (&jj)[UQ], int4 (&rr)[UQ]) {
+            if constexpr (SMALL) {
+#pragma unroll
+                for (int u = 0; u < UQ; ++u) {
+                    if constexpr (NS == 1) {
+                        const auto r = __builtin_amdgcn_raw_buffer_load_b96(rsrc_rec, jj[u] << 4, 0, 0);
+                        rr[u] = make_int4((int)r[0], (int)r[1], (int)r[2], 0);
+                    } else {
+                        const auto r = __builtin_amdgcn_raw_buffer_load_b128(rsrc_rec, jj[u] << 4, 0, 0);
+                        rr[u] = make_int4((int)r[0], (int)r[1], (int)r[2], (int)r[3]);
+                    }
+                }
+                return;
+            }
 #pragma unroll
             for (int u = 0; u < UQ; ++u) rr[u] = *reinterpret_cast<const int4 *>(recb + ((uint32_t)jj[u] << 4));
+        };
+        // The lane's pairs of one trip, in list order. SMALL: a pair outside
+        // takes a zero reciprocal instead of a branch (every term it adds is
+        // zero, so the sums are the same): with one wave per SIMD nothing
+        // hides the branches.
+        auto pairs = [&](const int4 (&rr)[UQ], int m) {
 #pragma unroll
             for (int u = 0; u < UQ; ++u) {
                 const float dx = (float)(int32_t)((uint32_t)ri.x - (uint32_t)rr[u].x);
@@ -132,8 +211,9 @@ __device__ inline void step_ds_body(const StepArgs &a, const BoxC &box, Ctl *ctl
                 const float dz = (float)(int32_t)((uint32_t)ri.z - (uint32_t)rr[u].z);
                 const float r2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
                 const int sj = rr[u].w;
-                if (m + u < iters && r2 < (NS == 1 ? rc2q : q_rc2(sj))) {
-                    const float ir2 = __builtin_amdgcn_rcpf(r2);
+                const bool in = m + u < iters && r2 < (NS == 1 ? rc2q : q_rc2(sj));
+                if (SMALL || in) {
+                    const float ir2 = SMALL ? (in ? __builtin_amdgcn_rcpf(r2) : 0.0f) : __builtin_amdgcn_rcpf(r2);
                     const float s2 = (NS == 1 ? sig2q : q_sig2(sj)) * ir2;
                     const float s6 = s2 * s2 * s2;
                     float t = (s6 * ir2) * fmaf(2.0f, s6, -1.0f);
@@ -145,14 +225,64 @@ __device__ inline void step_ds_body(const StepArgs &a, const BoxC &box, Ctl *ctl
                         if constexpr (NS == 1) {
                             sa = fmaf(s6, s6, sa);
                             sb += s6;
-                            an += 1;
+                            an += SMALL ? (in ? 1 : 0) : 1;
                         } else {
                             const float s12 = s6 * s6;
-                            sa += fmaf(t_eps4(sj), s12 - s6, -t_shift(sj));
+                            const float sh = SMALL ? (in ? t_shift(sj) : 0.0f) : t_shift(sj);
+                            sa += fmaf(t_eps4(sj), s12 - s6, -sh);
                             sb += t_eps24(sj) * fmaf(2.0f, s12, -s6);
                         }
                     }
                 }
+            }
+        };
+        if constexpr (SMALL) {
+            // Software pipeline over the trips of the wave's longest list: the
+            // records of one trip and the entries of the one after are in
+            // flight while a trip's pairs are evaluated, so a wave that has
+            // its SIMD to itself waits for about one memory latency in all
+            // instead of two per trip.
+            const int trips =
+                (__builtin_amdgcn_readlane((int)wave_max_last((uint32_t)iters), kWave - 1) + UQ - 1) / UQ;
+            if (trips > 0) {
+                int4 ra[UQ], rb[UQ];
+                gather(jn, ra);
+                entries(UQ * min(1, trips - 1), jn);
+                int t = 0;
+                for (; t + 2 < trips; t += 2) {
+                    gather(jn, rb);
+                    entries(UQ * (t + 2), jn);
+                    __builtin_amdgcn_sched_barrier(0);
+                    pairs(ra, UQ * t);
+                    __builtin_amdgcn_sched_barrier(0);
+                    gather(jn, ra);
+                    entries(UQ * min(t + 3, trips - 1), jn);
+                    __builtin_amdgcn_sched_barrier(0);
+                    pairs(rb, UQ * (t + 1));
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (t + 1 < trips) {
+                    gather(jn, rb);
+                    __builtin_amdgcn_sched_barrier(0);
+                    pairs(ra, UQ * t);
+                    pairs(rb, UQ * (t + 1));
+                } else {
+                    pairs(ra, UQ * t);
+                }
+            }
+        } else {
+            // Eight entries per trip (two 16-byte group loads per lane) keep
+            // more of the list stream in flight; groups past a list end read
+            // padding or other lists (valid indices) and are skipped. (Masking
+            // the loads of entries past a lane's list end instead, per entry,
+            // serialised them: 38.5 us against 30.3 us per launch at
+            // N = 256,000.)
+            for (int m = 0; m < iters; m += UQ) {
+                int jj[UQ];
+                int4 rr[UQ];
+                entries(m, jj);
+                gather(jj, rr);
+                pairs(rr, m);
             }
         }
         if constexpr (NS == 1) {
@@ -254,10 +384,14 @@ __device__ inline void step_ds_body(const StepArgs &a, const BoxC &box, Ctl *ctl
     }
     double pu = 0.0, pw = 0.0, pk = 0.0, ppx = 0.0, ppy = 0.0, ppz = 0.0;
     uint32_t dm = 0u;
-    if (valid && l == 0)
-        finish_ds<OBS, TH, PLAIN>(a, box, i, ri.w, st.xref[i], ds_load(st.dsw, i), fx, fy, fz, e, w, pu, pw, pk, ppx,
-                                  ppy, ppz, dm);
-    block_finish<OBS>(a, ctl, blk, pu, pw, pk, ppx, ppy, ppz, dm);
+    if (valid && l == 0) {
+        if constexpr (!SMALL) {
+            xr = st.xref[i];
+            ds = ds_load(st.dsw, i);
+        }
+        finish_ds<OBS, TH, PLAIN>(a, box, i, ri.w, xr, ds, fx, fy, fz, e, w, pu, pw, pk, ppx, ppy, ppz, dm);
+    }
+    block_finish<OBS, BS>(a, ctl, blk, pu, pw, pk, ppx, ppy, ppz, dm);
 }
 
 // PLAIN: the single-precision state (positions and velocities as single
@@ -283,6 +417,18 @@ constexpr void (*step_ds_kernel())(StepArgs) {
         return k_step_ds_mix<LANES, Q, OBS, PLAIN>;
     else
         return k_step_ds<NS, LANES, Q, OBS, TH, PLAIN>;
+}
+
+// The form for small boxes, two lanes per particle (the default layout). A
+// wave has its SIMD nearly to itself, so the kernel is a chain of latencies;
+// at 7,000 particles cycle stamps put it at 14,400 cycles (8,300 in the pair
+// loop, about six cycles per instruction; 20,100 and 11,700 before the loads
+// were pipelined and asked for ahead).
+template <int NS, bool OBS, bool TH, bool PLAIN>
+__global__ __launch_bounds__(kBlockSmall) void k_step_ds_small(StepArgs a) {
+    step_ds_body<NS, 2, true, OBS, TH, PLAIN, kBlockSmall, true>(a, a.box, a.st.ctl, xcd_remap(blockIdx.x, gridDim.x),
+                                                                 a.g.n, 0, a.box.ncell, blockIdx.x, gridDim.x,
+                                                                 a.st.rebuilt + a.slot);
 }
 
 // A batch of independent one-species cubic systems, each over its own run of
@@ -450,6 +596,32 @@ hipError_t launch_step(const Launch &L, int64_t step, int forced, int mode, int 
     const bool obs = (mode & kObserve) != 0;
     // The thermostat acts on "finalize" only.
     const bool th = L.dyn->thermo_on && (mode & kFinalize);
+    // At most two wavefronts per SIMD (256 particles per compute unit): nothing
+    // hides a wave's chain of loads then, and 1024-thread blocks leave compute
+    // units empty. Step kernel at 7,000 / 32,000 / 64,000 particles: 16.6 /
+    // 16.8 / 17.9 us with the form for large boxes, 9.6 / 10.0 / 13.0 us with
+    // this one; at 100,000 18.6 against 19.4 us, at 256,000 30.1 against 32.1.
+    const bool small = quanta && L.g->lanes == 2 && L.g->n <= (int64_t)256 * (L.g->ncu > 0 ? L.g->ncu : 256);
+    if (small) {
+        const dim3 gs((unsigned)L.g->max_blocks), bs(kBlockSmall);  // every row of partials is written
+#define STEP_SMALL(NS, OB)                                                           \
+    do {                                                                             \
+        if (th && plain)                                                             \
+            launch_k(L, k_step_ds_small<NS, OB, true, true>, gs, bs, a);             \
+        else if (th)                                                                 \
+            launch_k(L, k_step_ds_small<NS, OB, true, false>, gs, bs, a);            \
+        else if (plain)                                                              \
+            launch_k(L, k_step_ds_small<NS, OB, false, true>, gs, bs, a);            \
+        else                                                                         \
+            launch_k(L, k_step_ds_small<NS, OB, false, false>, gs, bs, a);           \
+    } while (0)
+        if (two && obs) STEP_SMALL(2, true);
+        else if (two) STEP_SMALL(2, false);
+        else if (obs) STEP_SMALL(1, true);
+        else STEP_SMALL(1, false);
+#undef STEP_SMALL
+        return hipGetLastError();
+    }
 #define STEP_DS(NS, LN, TH, PL)                                                                         \
     do {                                                                                                \
         if (quanta && obs)                                                                              \

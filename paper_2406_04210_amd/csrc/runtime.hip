@@ -199,7 +199,7 @@ struct Plan {
     int32_t cap_reserve;  // list slots per particle the workspace holds (>= cap): room to grow
     int nc[3];
     int ncell;
-    int max_blocks;
+    int max_blocks;       // rows of partials per step
     // byte offsets
     size_t off_rec[2], off_vel, off_frc, off_dsw[3], off_img, off_id,
         off_xref, off_nbr, off_cnt, off_ccount, off_cmem, off_cstart, off_rank, off_lin, off_scratch,
@@ -265,7 +265,7 @@ Plan make_plan(const ljmd_params *p) {
     pl.cell_cap = std::max<int32_t>(8, round_up(cc, 8));
     if (pl.cell_cap > 768) pl.cell_cap = 768;
     const int per_block = (step_block_threads(p->precision) / kWave) * (kWave / pl.lanes);
-    pl.max_blocks = (int)((p->n + per_block - 1) / per_block);
+    pl.max_blocks = (int)((p->n + per_block - 1) / per_block) * (step_block_threads(p->precision) / kRowThreads);
     lay_out(pl, p->precision, 1);
     return pl;
 }
@@ -944,7 +944,7 @@ BatchLayout batch_layout(const BatchGeom &bg, int nsys) {
     pl.cap_reserve = bg.cap;
     pl.cell_cap = bg.cell_cap;
     pl.lanes = bg.lanes;
-    pl.max_blocks = bg.nblocks;
+    pl.max_blocks = bg.nblocks * (kBlock / kRowThreads);
     lay_out(pl, LJMD_FP32_DS, nsys);
     size_t off = pl.total;
     auto take = [&](size_t bytes) {
@@ -1840,7 +1840,7 @@ int ljmd_batch_create(const ljmd_params *shared, const ljmd_system *sys, int32_t
     g.lanes = b->bg.lanes;
     g.nspecies = 1;
     g.prec = LJMD_FP32_DS;
-    g.max_blocks = b->bg.nblocks;
+    g.max_blocks = b->bl.pl.max_blocks;
     g.dim = 3;
     g.ncu = 256;
     if (b->device >= 0) {

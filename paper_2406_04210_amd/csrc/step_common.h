@@ -155,12 +155,14 @@ __device__ inline void wrap_ds(dsf &x, float Lhi, float Llo, int &im) {
 }
 
 // Block-level deterministic reduction of the six observable partials and the
-// displacement maximum; one row of partials per block.
-// Without OBS only the displacement maximum is reduced.
+// displacement maximum; one row of partials per kRowThreads threads (per
+// block when it is smaller). Without OBS only the displacement maximum is
+// reduced.
 template <bool OBS = true, int BS = kBlock>
 __device__ inline void block_finish(const StepArgs &a, Ctl *ctl, int blk, double u, double w, double k,
                                     double px, double py, double pz, uint32_t dmax) {
     constexpr int WPB = BS / kWave;
+    constexpr int ROWS = BS > kRowThreads ? BS / kRowThreads : 1, WPR = WPB / ROWS;
     __shared__ double red[WPB][6];
     __shared__ uint32_t redm[WPB];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -178,11 +180,12 @@ __device__ inline void block_finish(const StepArgs &a, Ctl *ctl, int blk, double
         redm[wv] = dmax;
     }
     __syncthreads();
-    if (OBS && threadIdx.x < kNP) {
+    if (OBS && threadIdx.x < ROWS * kNP) {
+        const int r = threadIdx.x / kNP, c = threadIdx.x % kNP;
         double s = 0.0;
-        if (threadIdx.x < 6)
-            for (int q = 0; q < WPB; ++q) s += red[q][threadIdx.x];
-        a.st.partials[((size_t)a.slot * a.g.max_blocks + blk) * kNP + threadIdx.x] = s;
+        if (c < 6)
+            for (int q = 0; q < WPR; ++q) s += red[r * WPR + q][c];
+        a.st.partials[((size_t)a.slot * a.g.max_blocks + (size_t)blk * ROWS) * kNP + threadIdx.x] = s;
     }
     if (threadIdx.x == 0 && (a.mode & kIntegrate)) {
         uint32_t m = 0;
