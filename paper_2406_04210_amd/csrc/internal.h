@@ -363,6 +363,9 @@ hipError_t launch_bin(const Launch &L, int64_t step, int forced);
 hipError_t launch_canon(const Launch &L, int64_t step, int forced);
 hipError_t launch_resort(const Launch &L);
 hipError_t launch_nlist(const Launch &L, int64_t step, int forced);
+// Small boxes: binning, canonical order and list build in one launch.
+bool rebuild_in_one_launch(const Geom &g, const BoxC &box);
+hipError_t launch_rebuild_small(const Launch &L, int64_t step, int forced);
 // mode bits for launch_step
 // kObserve: the step's observable partials (energy, virial, kinetic energy,
 // momentum) will be reduced; without it the one-species cubic kernels skip

@@ -863,6 +863,197 @@ __global__ __launch_bounds__(kNlWaves * kWave, 6) void k_nlist(State st, Geom g,
     }
 }
 
+// ---- small boxes: the whole rebuild in one launch --------------------------
+// Up to kRebuildSmallN particles, one block per home cell finds its candidates
+// by scanning every particle's record instead of reading cells filled by an
+// earlier kernel, so binning, canonical order and list build need no pass over
+// the device between them:
+//   1. each wave scans one contiguous share of the particles, keeps those in
+//      the cells around the home cell (index and stencil cell, in index order)
+//      and counts them per stencil cell;
+//   2. the counts become each wave's first position in every stencil cell;
+//   3. the waves place their survivors: stencil cell by stencil cell, indices
+//      ascending -- the candidate order of k_nlist, so the lists are the same
+//      entry for entry;
+//   4. the home particles are dealt to the waves, which test them against all
+//      candidates as k_nlist does.
+// What it replaces is bound by latency at these sizes: three launches a step
+// that mostly return at once, and per rebuild two passes of ~5 us and one wave
+// per cell (64 waves at 2,048 particles: 91 us in FP64). The scan costs
+// n * cells / 64 wave trips. Per step at 2,000 / 12,000 particles: FP32 21.9 /
+// 19.6 -> 13.2 / 15.4 us, FP64 29.0 / 25.5 -> 16.5 / 19.8 us. The limit is the
+// 64 KiB of LDS a block may ask for (five bytes per particle).
+constexpr int kRebuildSmallN = 12288;
+constexpr int kRebuildSmallWaves = 16;
+
+__host__ __device__ inline int rebuild_small_share(int64_t n) {
+    return (int)(((n + kRebuildSmallWaves - 1) / kRebuildSmallWaves + kWave - 1) / kWave * kWave);
+}
+static size_t rebuild_small_lds(int64_t n) {
+    const size_t slots = (size_t)rebuild_small_share(n) * kRebuildSmallWaves;
+    return slots * (2 * sizeof(uint16_t) + sizeof(uint8_t));
+}
+
+template <int PREC, int NS, bool QC, int LG>
+__global__ __launch_bounds__(kRebuildSmallWaves * kWave) void k_rebuild_small(State st, Geom g, BoxC box, PairC pc,
+                                                                            int cur, int64_t step, int forced,
+                                                                            float thr2) {
+    using CR = CellRec<PREC>;
+    using T = typename CR::T;
+    constexpr int W = kRebuildSmallWaves, CH = NlistChunk<PREC>::CH;
+    if (blockIdx.x == 0 && threadIdx.x == 0) st.ctl->maxd[(step + 1) & 1] = 0u;
+    if (halted(st.ctl) || !rebuild_due(st.ctl, step, forced, thr2)) return;
+    if (blockIdx.x == 0 && threadIdx.x == 0) st.ctl->rebuilds += 1;
+    extern __shared__ uint16_t small_sm[];
+    __shared__ int hist[W][32];      // survivors per wave and stencil cell, then positions
+    __shared__ int total[3];         // candidates; first home particle among them, home particles
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int n = (int)g.n, share = rebuild_small_share(n);
+    uint16_t *surv = small_sm + wv * share, *ordered = small_sm + W * share;
+    uint8_t *bkt = (uint8_t *)(small_sm + 2 * W * share) + wv * share;
+    const auto *__restrict__ rec = records<PREC>(st, cur);
+
+    // The stencil: per axis cells s0 .. s0 + n3 - 1 (wrapped), the whole axis
+    // where it has fewer than three.
+    const int lin = st.cell_lin[blockIdx.x];
+    const int cc[3] = {lin / (box.nc[1] * box.nc[2]), (lin / box.nc[2]) % box.nc[1], lin % box.nc[2]};
+    int s0[3], n3[3];
+    for (int a = 0; a < 3; ++a) {
+        const bool wide = box.nc[a] >= 3;
+        s0[a] = wide ? (cc[a] == 0 ? box.nc[a] - 1 : cc[a] - 1) : 0;
+        n3[a] = wide ? 3 : box.nc[a];
+    }
+    auto offset = [&](int c, int a) {
+        const int d = c - s0[a];
+        return d < 0 ? d + box.nc[a] : d;
+    };
+    const int home = (offset(cc[0], 0) * n3[1] + offset(cc[1], 1)) * n3[2] + offset(cc[2], 2);
+
+    if (lane < 32) hist[wv][lane] = 0;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const int i0 = wv * share, i1 = min(n, i0 + share);
+    int kept = 0;
+    constexpr int U = 4;
+    for (int b0 = i0; b0 < i1; b0 += U * kWave) {
+        T r[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) r[u] = rec[min(b0 + u * kWave + lane, n - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = b0 + u * kWave + lane;
+            uint32_t q[3];
+            rec_q(r[u], box, q);
+            const int dx = offset((int)(((uint64_t)q[0] * (uint32_t)box.nc[0]) >> 32), 0);
+            const int dy = offset((int)(((uint64_t)q[1] * (uint32_t)box.nc[1]) >> 32), 1);
+            const int dz = offset((int)(((uint64_t)q[2] * (uint32_t)box.nc[2]) >> 32), 2);
+            const bool in = i < i1 && dx < n3[0] && dy < n3[1] && dz < n3[2];
+            const unsigned long long mask = __ballot(in);
+            if (in) {
+                const int b = (dx * n3[1] + dy) * n3[2] + dz;
+                const int at = kept + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+                surv[at] = (uint16_t)i;
+                bkt[at] = (uint8_t)b;
+                atomicAdd(&hist[wv][b], 1);
+            }
+            kept += __popcll(mask);
+        }
+    }
+    __syncthreads();
+    if (wv == 0) {
+        int sum = 0;
+        if (lane < 32)
+            for (int w = 0; w < W; ++w) sum += hist[w][lane];
+        int incl = sum;
+        for (int o = 1; o < 32; o <<= 1) {
+            const int y = __shfl_up(incl, o);
+            if (lane >= o) incl += y;
+        }
+        int at = incl - sum;
+        if (lane == 31) total[0] = incl;
+        if (lane == home) {
+            total[1] = at;
+            total[2] = sum;
+            if (sum > g.cell_cap) atomicOr(&st.ctl->flags, kErrCell);
+        }
+        if (lane < 32)
+            for (int w = 0; w < W; ++w) {
+                const int c = hist[w][lane];
+                hist[w][lane] = at;
+                at += c;
+            }
+    }
+    __syncthreads();
+    for (int k0 = 0; k0 < kept; k0 += kWave) {
+        const bool act = k0 + lane < kept;
+        const int b = act ? bkt[k0 + lane] : -1;
+        const int base = act ? hist[wv][b] : 0;
+        unsigned long long pending = __ballot(act);
+        int rank = 0;
+        while (pending) {
+            const int leader = __ffsll(pending) - 1;
+            const int bl = __builtin_amdgcn_readlane(b, leader);
+            const unsigned long long same = __ballot(b == bl);
+            if (b == bl)
+                rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32),
+                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
+            if (lane == leader) hist[wv][b] = base + __popcll(same);
+            pending &= ~same;
+        }
+        if (act) ordered[base + rank] = surv[k0 + lane];
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    const int ncand = __builtin_amdgcn_readfirstlane(total[0]), hs = __builtin_amdgcn_readfirstlane(total[1]),
+              m = __builtin_amdgcn_readfirstlane(total[2]);
+    for (int h0 = 0; h0 < m; h0 += kWave) {
+        const int hm = min(m - h0, kWave);
+        const uint64_t homes =
+            (0x0001000100010001ull << wv) & (hm >= kWave ? ~0ull : ((1ull << hm) - 1ull));
+        static_assert(W == 16, "home particles are dealt to 16 waves");
+        if (homes == 0ull) continue;
+        T hrec = T{};
+        if (lane < hm) {
+            const int i = ordered[hs + h0 + lane];
+            hrec = CR::pack(rec[i], i);
+        }
+        int kreg = 0;
+        for (int cb = 0; cb < ncand; cb += CH * kWave) {
+            const int nbk = min(CH, (ncand - cb + kWave - 1) / kWave);
+            T cand[CH];
+            bool cv[CH];
+            uint32_t thr[CH], thr1[CH];
+#pragma unroll
+            for (int b = 0; b < CH; ++b) {
+                cv[b] = false;
+                cand[b] = T{};
+                thr[b] = thr1[b] = 0u;
+                if (b >= nbk) continue;
+                const int t = cb + b * kWave + lane;
+                cv[b] = t < ncand;
+                const int j = cv[b] ? ordered[t] : 0;
+                cand[b] = CR::pack(rec[j], j);
+            }
+#pragma unroll
+            for (int b = 0; b < CH; ++b) {
+                if (b >= nbk) break;
+                nlist_bounds<PREC, NS, QC>(box, pc, cand[b], cv[b], thr[b], thr1[b]);
+            }
+            nlist_homes<PREC, NS, QC, LG, CH>(st, g, box, pc, hrec, kreg, homes, cand, cv, thr, thr1, nbk);
+        }
+        if ((homes >> lane) & 1ull) {
+            const int i = CR::index(hrec);
+            uint32_t q[3];
+            rec_q(hrec, box, q);
+            st.nbr_cnt[i] = kreg;
+            st.xref[i] = make_int4((int)q[0], (int)q[1], (int)q[2], CR::species(hrec));
+            if (kreg > g.cap) atomicOr(&st.ctl->flags, kErrList);
+        }
+    }
+}
+
 // ---- batches of systems -------------------------------------------------
 // Plan entry k holds flattened items [off[k], off[k + 1]): the last k with
 // off[k] <= t.
@@ -1110,6 +1301,37 @@ hipError_t launch_nlist(const Launch &L, int64_t step, int forced) {
     } else {
         if (L.g->nspecies == 1) nlist_launch<LJMD_FP32_DS, 1>(L, step, forced);
         else nlist_launch<LJMD_FP32_DS, 2>(L, step, forced);
+    }
+    return hipGetLastError();
+}
+
+bool rebuild_in_one_launch(const Geom &g, const BoxC &box) {
+    return !g.all_pairs && g.n <= kRebuildSmallN && box.reach == 1;
+}
+
+template <int PREC, int NS>
+static void rebuild_small_launch(const Launch &L, int64_t step, int forced) {
+    const dim3 grid((unsigned)L.box->ncell), block(kRebuildSmallWaves * kWave);
+    const size_t lds = rebuild_small_lds(L.g->n);
+    constexpr bool F32 = PREC == LJMD_FP32_DS;
+    if (F32 && L.box->cubic && L.g->lanes == 2)
+        hipLaunchKernelGGL((k_rebuild_small<PREC, NS, F32, 1>), grid, block, lds, L.stream, *L.st, *L.g, *L.box, *L.pc,
+                           L.cur, step, forced, L.dyn->thr2);
+    else if (F32 && L.box->cubic)
+        hipLaunchKernelGGL((k_rebuild_small<PREC, NS, F32, -1>), grid, block, lds, L.stream, *L.st, *L.g, *L.box,
+                           *L.pc, L.cur, step, forced, L.dyn->thr2);
+    else
+        hipLaunchKernelGGL((k_rebuild_small<PREC, NS, false, -1>), grid, block, lds, L.stream, *L.st, *L.g, *L.box,
+                           *L.pc, L.cur, step, forced, L.dyn->thr2);
+}
+
+hipError_t launch_rebuild_small(const Launch &L, int64_t step, int forced) {
+    if (L.g->prec == LJMD_FP64) {
+        if (L.g->nspecies == 1) rebuild_small_launch<LJMD_FP64, 1>(L, step, forced);
+        else rebuild_small_launch<LJMD_FP64, 2>(L, step, forced);
+    } else {
+        if (L.g->nspecies == 1) rebuild_small_launch<LJMD_FP32_DS, 1>(L, step, forced);
+        else rebuild_small_launch<LJMD_FP32_DS, 2>(L, step, forced);
     }
     return hipGetLastError();
 }

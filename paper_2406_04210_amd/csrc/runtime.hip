@@ -483,6 +483,7 @@ int rebuild_sequence(ljmd_ctx *c, int64_t step, int forced, bool resort) {
     if (c->g.all_pairs) return LJMD_OK;  // no lists to build
     Launch L = launcher(c);
     hipError_t e;
+    const bool one = rebuild_in_one_launch(c->g, c->box);
     if (resort) {
         {
             Bracket b(c, 1);
@@ -494,10 +495,14 @@ int rebuild_sequence(ljmd_ctx *c, int64_t step, int forced, bool resort) {
             if ((e = launch_resort(L)) != hipSuccess) return hip_fail(c, e, "resort");
         }
         Bracket b(c, 1);
-        if ((e = launch_nlist(L, step, forced)) != hipSuccess) return hip_fail(c, e, "nlist");
-        return LJMD_OK;
+        e = one ? launch_rebuild_small(L, step, forced) : launch_nlist(L, step, forced);
+        return e == hipSuccess ? LJMD_OK : hip_fail(c, e, "nlist");
     }
     Bracket b(c, 1);
+    if (one) {
+        e = launch_rebuild_small(L, step, forced);
+        return e == hipSuccess ? LJMD_OK : hip_fail(c, e, "rebuild");
+    }
     if ((e = launch_bin(L, step, forced)) != hipSuccess) return hip_fail(c, e, "bin");
     if ((e = launch_canon(L, step, forced)) != hipSuccess) return hip_fail(c, e, "canon");
     if ((e = launch_nlist(L, step, forced)) != hipSuccess) return hip_fail(c, e, "nlist");
