@@ -190,16 +190,17 @@ __global__ __launch_bounds__(kApFinishBlock) void k_ap_finish(StepArgs a, const 
     const bool valid = i < a.g.n;
     // Everything up to the step tail only reads, so it goes ahead of the halt
     // check, whose latency then overlaps the loads.
-    double4 r64;
+    double4 r64, v64;
     int si = 0;
     int4 xr;
     DsState ds;
     if (valid) {
+        xr = a.st.xref[i];
         if constexpr (PREC == LJMD_FP64) {
             r64 = a.st.rec64[a.cur][i];
+            v64 = a.st.vel64[i];
         } else {
             si = a.st.recq[a.cur][i].w;
-            xr = a.st.xref[i];
             ds = ds_load(a.st.dsw, i);
         }
     }
@@ -235,7 +236,7 @@ __global__ __launch_bounds__(kApFinishBlock) void k_ap_finish(StepArgs a, const 
     if (halted_record(ctl, a.step, blockIdx.x == 0)) return;
     if (valid) {
         if constexpr (PREC == LJMD_FP64)
-            finish_fp64<TH>(a, a.box, i, r64, f.x, f.y, f.z, ew.x, ew.y, pu, pw, pk, ppx, ppy, ppz, dm);
+            finish_fp64<TH>(a, a.box, i, r64, v64, xr, f.x, f.y, f.z, ew.x, ew.y, pu, pw, pk, ppx, ppy, ppz, dm);
         else
             finish_ds<true, TH, PREC == LJMD_FP32>(a, a.box, i, si, xr, ds, f.x, f.y, f.z, ew.x, ew.y, pu, pw, pk,
                                                    ppx, ppy, ppz, dm);

@@ -444,10 +444,16 @@ __global__ __launch_bounds__(kBlock) void k_batch_step(StepArgs a, const SysC *s
 }
 
 // ---------------------------------------------------------------- FP64 ---
-template <int NS, int LANES, bool TH>
-__global__ __launch_bounds__(kBlockF64) void k_step_fp64(StepArgs a) {
+// SMALL: the form for boxes that leave the chip's wave slots mostly empty, as
+// in the single-precision body: loads through buffer descriptors, everything
+// outside the trips asked for at once, one trip's records and the next trip's
+// entries in flight while a trip's pairs are evaluated. The same sums in the
+// same order.
+template <int NS, int LANES, bool TH, bool SMALL>
+__device__ inline void step_fp64_body(const StepArgs &a) {
     constexpr int P = kWave / LANES;
     constexpr int WPB = kBlockF64 / kWave;
+    constexpr int U = 4;  // list entries of a lane per trip: one group load
     const State &st = a.st;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int blk = xcd_remap(blockIdx.x, gridDim.x);
@@ -455,29 +461,76 @@ __global__ __launch_bounds__(kBlockF64) void k_step_fp64(StepArgs a) {
     const int l = lane % LANES;
     const int64_t i = chunk * P + lane / LANES;
     const bool valid = i < a.g.n;
+    const double4 *__restrict__ rec = st.rec64[a.cur];
+    const int32_t *__restrict__ nb = st.nbr + chunk * (int64_t)(P * a.g.cap) + 4 * lane;
+    double4 ri = make_double4(0, 0, 0, 0);
+    int cnt = 0;
+    [[maybe_unused]] __amdgpu_buffer_rsrc_t rsrc_rec, rsrc_nb;
+    [[maybe_unused]] int jn[U];
+    [[maybe_unused]] double4 vel;
+    [[maybe_unused]] int4 xr;
+    auto entries = [&](int m, int (&jj)[U]) {
+        if constexpr (SMALL) {
+            const auto g = __builtin_amdgcn_raw_buffer_load_b128(rsrc_nb, lane << 4, m << 8, 0);
+#pragma unroll
+            for (int u = 0; u < U; ++u) jj[u] = (int)g[u];
+        } else {
+            const int4 g = *reinterpret_cast<const int4 *>(nb + ((int64_t)(m >> 2) << 8));
+            jj[0] = g.x, jj[1] = g.y, jj[2] = g.z, jj[3] = g.w;
+        }
+    };
+    auto load4 = [](const __amdgpu_buffer_rsrc_t &rs, int off) {
+        const auto p = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
+        const auto q = __builtin_amdgcn_raw_buffer_load_b128(rs, off + 16, 0, 0);
+        auto d = [](uint32_t lo, uint32_t hi) { return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo)); };
+        return make_double4(d(p[0], p[1]), d(p[2], p[3]), d(q[0], q[1]), d(q[2], q[3]));
+    };
+    auto gather = [&](const int (&jj)[U], double4 (&rr)[U]) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if constexpr (SMALL) rr[u] = load4(rsrc_rec, jj[u] << 5);
+            else rr[u] = rec[jj[u]];
+        }
+    };
+    if constexpr (SMALL) {
+        auto rsrc = [](const void *p, int64_t bytes) {
+            return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, kRawBuffer);
+        };
+        const int64_t wchunk = __builtin_amdgcn_readfirstlane((int)chunk);
+        rsrc_rec = rsrc(rec, a.g.n << 5);
+        rsrc_nb = rsrc(st.nbr + wchunk * (P * a.g.cap), wchunk * P < a.g.n ? P * a.g.cap * 4 + kListPad * 4 : 0);
+        const uint32_t c = __builtin_amdgcn_raw_buffer_load_b32(rsrc(st.nbr_cnt, a.g.n << 2), (int)i << 2, 0, 0);
+        ri = load4(rsrc_rec, (int)i << 5);
+        entries(0, jn);
+        const auto x = __builtin_amdgcn_raw_buffer_load_b128(rsrc(st.xref, a.g.n << 4), (int)i << 4, 0, 0);
+        vel = load4(rsrc(st.vel64, a.g.n << 5), (int)i << 5);
+        // One word of every 64-byte line of the kernel arguments.
+        const auto *arg = (const __attribute__((address_space(4))) int *)__builtin_amdgcn_kernarg_segment_ptr();
+        int touch = 0;
+#pragma unroll
+        for (int k = 0; k < (int)((sizeof(StepArgs) + 63) / 64); ++k) touch |= arg[k * 16];
+        asm volatile("" ::"s"(touch));
+        __builtin_amdgcn_sched_barrier(0);
+        xr = make_int4((int)x[0], (int)x[1], (int)x[2], (int)x[3]);
+        cnt = valid ? (int)c : 0;
+    }
     if (halted_record(a.st.ctl, a.step, blockIdx.x == 0)) return;
     step_housekeeping(a, a.st.ctl, 0, a.box.ncell, blockIdx.x, gridDim.x, a.st.rebuilt + a.slot);
-
-    const double4 *__restrict__ rec = st.rec64[a.cur];
-    double4 ri = valid ? rec[i] : make_double4(0, 0, 0, 0);
+    if constexpr (!SMALL) {
+        if (valid) {
+            ri = rec[i];
+            cnt = st.nbr_cnt[i];
+        }
+    }
     const int si = (int)ri.w;
-    int cnt = valid ? st.nbr_cnt[i] : 0;
     cnt = cnt < a.g.cap ? cnt : a.g.cap;
-    const int32_t *__restrict__ nb = st.nbr + chunk * (int64_t)(P * a.g.cap) + 4 * lane;
     const int iters = cnt > l ? (cnt - l + LANES - 1) / LANES : 0;
     double fx = 0, fy = 0, fz = 0, e = 0, w = 0;
     const PairRow<double> t_rc2(a.pc.rc2, si), t_sig2(a.pc.sig2, si), t_eps24(a.pc.eps24, si),
         t_eps4(a.pc.eps4, si), t_shift(a.pc.shift, si);
-    constexpr int U = 4;
-    for (int m = 0; m < iters; m += U) {
-        // One 16-byte group load per lane: its four entries m .. m+3 (entries
-        // past the list end are valid indices and are skipped).
-        static_assert(U == 4, "one entry group per trip");
-        const int4 grp = *reinterpret_cast<const int4 *>(nb + ((int64_t)(m >> 2) << 8));
-        const int jj[U] = {grp.x, grp.y, grp.z, grp.w};
-        double4 rr[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) rr[u] = rec[jj[u]];
+    // The lane's pairs of one trip, in list order (entries past the list end
+    // are valid indices and are skipped).
+    auto pairs = [&](const double4 (&rr)[U], int m) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (m + u >= iters) continue;
@@ -503,22 +556,79 @@ __global__ __launch_bounds__(kBlockF64) void k_step_fp64(StepArgs a) {
                 w = fma(fs, r2, w);
             }
         }
+    };
+    if constexpr (SMALL) {
+        const int trips = (__builtin_amdgcn_readlane((int)wave_max_last((uint32_t)iters), kWave - 1) + U - 1) / U;
+        if (trips > 0) {
+            double4 ra[U], rb[U];
+            gather(jn, ra);
+            entries(U * min(1, trips - 1), jn);
+            int t = 0;
+            for (; t + 2 < trips; t += 2) {
+                gather(jn, rb);
+                entries(U * (t + 2), jn);
+                __builtin_amdgcn_sched_barrier(0);
+                pairs(ra, U * t);
+                __builtin_amdgcn_sched_barrier(0);
+                gather(jn, ra);
+                entries(U * min(t + 3, trips - 1), jn);
+                __builtin_amdgcn_sched_barrier(0);
+                pairs(rb, U * (t + 1));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (t + 1 < trips) {
+                gather(jn, rb);
+                __builtin_amdgcn_sched_barrier(0);
+                pairs(ra, U * t);
+                pairs(rb, U * (t + 1));
+            } else {
+                pairs(ra, U * t);
+            }
+        }
+    } else {
+        for (int m = 0; m < iters; m += U) {
+            int jj[U];
+            double4 rr[U];
+            entries(m, jj);
+            gather(jj, rr);
+            pairs(rr, m);
+        }
     }
     if constexpr (LANES > 1) {
-#pragma unroll
-        for (int o = LANES / 2; o > 0; o >>= 1) {
-            fx += __shfl_xor(fx, o);
-            fy += __shfl_xor(fy, o);
-            fz += __shfl_xor(fz, o);
-            e += __shfl_xor(e, o);
-            w += __shfl_xor(w, o);
-        }
+        // The particle's lanes exchange their sums: wide steps by shuffles,
+        // within a quad by DPP moves (no LDS round trip).
+        auto xsum = [](double &v) {
+            if constexpr (LANES >= 16) v += __shfl_xor(v, 8);
+            if constexpr (LANES >= 8) v += __shfl_xor(v, 4);
+            if constexpr (LANES >= 4) v += dpp_d<kDppXor2>(v);
+            v += dpp_d<kDppXor1>(v);
+        };
+        xsum(fx);
+        xsum(fy);
+        xsum(fz);
+        xsum(e);
+        xsum(w);
     }
     double pu = 0.0, pw = 0.0, pk = 0.0, ppx = 0.0, ppy = 0.0, ppz = 0.0;
     uint32_t dm = 0u;
-    if (valid && l == 0)
-        finish_fp64<TH>(a, a.box, i, ri, fx, fy, fz, e, w, pu, pw, pk, ppx, ppy, ppz, dm);
+    if (valid && l == 0) {
+        if constexpr (!SMALL) {
+            vel = st.vel64[i];
+            xr = st.xref[i];
+        }
+        finish_fp64<TH>(a, a.box, i, ri, vel, xr, fx, fy, fz, e, w, pu, pw, pk, ppx, ppy, ppz, dm);
+    }
     block_finish<true, kBlockF64>(a, a.st.ctl, blk, pu, pw, pk, ppx, ppy, ppz, dm);
+}
+
+template <int NS, int LANES, bool TH>
+__global__ __launch_bounds__(kBlockF64) void k_step_fp64(StepArgs a) {
+    step_fp64_body<NS, LANES, TH, false>(a);
+}
+// Small boxes, four lanes per particle (the default layout).
+template <int NS, bool TH>
+__global__ __launch_bounds__(kBlockF64) void k_step_fp64_small(StepArgs a) {
+    step_fp64_body<NS, 4, TH, true>(a);
 }
 
 // Start of a run: "integrate" from the stored forces of the current step
@@ -533,7 +643,8 @@ __device__ inline void integrate_body(const StepArgs &a, const BoxC &box, Ctl *c
     if (i < i_end) {
         if constexpr (PREC == LJMD_FP64) {
             const double4 f = st.frc64[i];
-            finish_fp64<false>(a, box, i, st.rec64[a.cur][i], f.x, f.y, f.z, 0.0, 0.0, pu, pw, pk, ppx, ppy, ppz, dm);
+            finish_fp64<false>(a, box, i, st.rec64[a.cur][i], st.vel64[i], st.xref[i], f.x, f.y, f.z, 0.0, 0.0, pu, pw,
+                               pk, ppx, ppy, ppz, dm);
         } else {
             const float4 f = st.frc32[i];
             finish_ds<false, false, PREC == LJMD_FP32>(a, box, i, st.recq[a.cur][i].w, st.xref[i],
@@ -601,7 +712,8 @@ hipError_t launch_step(const Launch &L, int64_t step, int forced, int mode, int 
     // units empty. Step kernel at 7,000 / 32,000 / 64,000 particles: 16.6 /
     // 16.8 / 17.9 us with the form for large boxes, 9.6 / 10.0 / 13.0 us with
     // this one; at 100,000 18.6 against 19.4 us, at 256,000 30.1 against 32.1.
-    const bool small = quanta && L.g->lanes == 2 && L.g->n <= (int64_t)256 * (L.g->ncu > 0 ? L.g->ncu : 256);
+    const bool few_waves = L.g->n <= (int64_t)256 * (L.g->ncu > 0 ? L.g->ncu : 256);
+    const bool small = quanta && L.g->lanes == 2 && few_waves;
     if (small) {
         const dim3 gs((unsigned)L.g->max_blocks), bs(kBlockSmall);  // every row of partials is written
 #define STEP_SMALL(NS, OB)                                                           \
@@ -620,6 +732,16 @@ hipError_t launch_step(const Launch &L, int64_t step, int forced, int mode, int 
         else if (obs) STEP_SMALL(1, true);
         else STEP_SMALL(1, false);
 #undef STEP_SMALL
+        return hipGetLastError();
+    }
+    // FP64, by the same rule (four waves per SIMD then): step kernel at 2,000 /
+    // 32,000 / 64,000 particles 11.1 / 13.3 / 18.2 us with the other form, 9.2 /
+    // 11.9 / 17.7 us with this one; at 256,000 48.7 against 49.8.
+    if (!ds && L.g->lanes == 4 && few_waves) {
+        if (two && th) launch_k(L, k_step_fp64_small<2, true>, grid, block, a);
+        else if (two) launch_k(L, k_step_fp64_small<2, false>, grid, block, a);
+        else if (th) launch_k(L, k_step_fp64_small<1, true>, grid, block, a);
+        else launch_k(L, k_step_fp64_small<1, false>, grid, block, a);
         return hipGetLastError();
     }
 #define STEP_DS(NS, LN, TH, PL)                                                                         \

@@ -311,16 +311,16 @@ __device__ inline void finish_ds(const StepArgs &a, const BoxC &box, int64_t i, 
     if (a.mode & kStoreForce) st.frc32[i] = make_float4(fx, fy, fz, 0.f);
 }
 
-// The same tail for the FP64 path (record ri: position and species of slot i).
+// The same tail for the FP64 path (record ri: position and species of slot i;
+// velocity v and list reference xr as read by the caller).
 template <bool TH>
-__device__ inline void finish_fp64(const StepArgs &a, const BoxC &box, int64_t i, const double4 &ri, double fx,
-                                   double fy, double fz, double e, double w, double &pu, double &pw, double &pk,
-                                   double &ppx, double &ppy, double &ppz, uint32_t &dm) {
+__device__ inline void finish_fp64(const StepArgs &a, const BoxC &box, int64_t i, const double4 &ri, double4 v,
+                                   const int4 &xr, double fx, double fy, double fz, double e, double w, double &pu,
+                                   double &pw, double &pk, double &ppx, double &ppy, double &ppz, uint32_t &dm) {
     const State &st = a.st;
     const int si = (int)ri.w;
     const double c = by_s(si, a.dyn.hdt_m);
     const double mass = by_s(si, a.dyn.mass);
-    double4 v = st.vel64[i];
     if (a.mode & kFinalize) {
         v.x += c * fx;
         v.y += c * fy;
@@ -362,7 +362,6 @@ __device__ inline void finish_fp64(const StepArgs &a, const BoxC &box, int64_t i
             st.img[i] = make_int4(im.x + d[0], im.y + d[1], im.z + d[2], 0);
         }
         st.rec64[a.cur ^ 1][i] = make_double4(x[0], x[1], x[2], ri.w);
-        const int4 xr = st.xref[i];
         const float ddx = disp_q(q_from_d(x[0], box.S[0]), (uint32_t)xr.x, box.qs_hi[0], box.qs_lo[0]);
         const float ddy = disp_q(q_from_d(x[1], box.S[1]), (uint32_t)xr.y, box.qs_hi[1], box.qs_lo[1]);
         const float ddz = disp_q(q_from_d(x[2], box.S[2]), (uint32_t)xr.z, box.qs_hi[2], box.qs_lo[2]);
