@@ -132,7 +132,7 @@ struct State {
                           // ascending by index after canonicalisation
     int32_t *cell_start;  // [ncell + 1] exclusive scan of counts (resort only)
     int32_t *rank_of;     // [ncell] Hilbert rank of the cell with linear index (ix*ny+iy)*nz+iz
-    int32_t *cell_lin;    // [ncell] linear index of the cell with a given Hilbert rank
+    int32_t *cell_pos;    // [ncell] grid position of the cell with a given Hilbert rank: ix << 20 | iy << 10 | iz
     uint8_t *scratch;     // resort staging
     double *partials;     // [kRing][max_blocks][kNP] per-block observable partials
     int32_t *rebuilt;     // [kRing] 1 if the list was rebuilt before that step's force

@@ -351,10 +351,14 @@ __device__ inline float cand_r2q(const int4 &ri, const int4 &rj) {
 // and the list stores are never waited on.
 template <int PREC, bool FILT = false>
 struct NlistChunk {
-    // 64-candidate blocks per chunk (FILT: blocks loaded per round and per
-    // queue drain; six keep the kernel within 96 VGPRs, five waves per SIMD,
-    // and its two queues within 6 KiB of LDS per wave)
-    static constexpr int CH = FILT ? 6 : (PREC == LJMD_FP64 ? 4 : 8);
+    // 64-candidate blocks tested at a time, and loaded per round. With the
+    // box reduction (FILT) the queues of a wave hold CH + CL blocks each: six
+    // and five keep its LDS under 6 KiB (six blocks of four waves per compute
+    // unit) and liquid densities within two load rounds per cell. (Eight waves
+    // per SIMD with four and three, seven with five and three: 88 and 81 us
+    // per rebuild at N = 256,000 against 80.)
+    static constexpr int CH = PREC == LJMD_FP64 ? 4 : (FILT ? 6 : 8);
+    static constexpr int CL = PREC == LJMD_FP64 ? 4 : (FILT ? 5 : 8);
 };
 
 // Waves per list-build block, and blocks per compute unit: with up to
@@ -513,35 +517,86 @@ __device__ inline void nlist_bounds(const BoxC &box, const PairC &pc, const type
     }
 }
 
-// Candidates per queue of the reduced list build: a chunk of CH blocks is
-// appended to queues holding fewer than CH blocks' worth.
-template <int CH>
-struct NlistQueue {
-    static constexpr int kCap = 2 * CH * kWave;
+// LDS of one wave of the list build. Reduced build (FILT): two queues of
+// candidate indices, each appended to by CL blocks while it holds fewer than
+// CH. In both forms the stencil cells that hold anything (flattened index,
+// offset of the first candidate) and the first candidates of a load round,
+// one bit each.
+template <int PREC, bool FILT>
+struct NlistLds {
+    using C = NlistChunk<PREC, FILT>;
+    static constexpr int kCap = FILT ? (C::CH + C::CL) * kWave : 1;
+    int32_t queue[FILT ? 2 : 1][kCap];
+    int2 cells[kWave];
+    uint32_t heads[2 * C::CL];
 };
 
+// The reduced build's test of the cnt candidates at the front of queue qg,
+// reloaded from their records, against the home particles of the lanes in
+// `homes`. (Collecting a home particle's hits in LDS and storing them 64 at a
+// time, six vector instructions fewer per 64 candidates, measured slower: the
+// LDS round trips per home particle cost more.)
+template <int PREC, int NS, int LG>
+__device__ inline void nlist_homes_queued(const State &st, const Geom &g, const BoxC &box, const PairC &pc,
+                                          const typename CellRec<PREC>::T &hrec, int &kreg, uint64_t homes,
+                                          const int32_t *qg, int cnt,
+                                          const typename CellRec<PREC>::T *__restrict__ rec) {
+    using CR = CellRec<PREC>;
+    using T = typename CR::T;
+    constexpr int CH = NlistChunk<PREC, true>::CH;
+    const int lane = threadIdx.x & 63;
+    const int nbk = (cnt + kWave - 1) / kWave;
+    T cand[CH];
+    bool cv[CH];
+    uint32_t thr[CH], thr1[CH];
+#pragma unroll
+    for (int b = 0; b < CH; ++b) {
+        cv[b] = false;
+        cand[b] = T{};
+        thr[b] = thr1[b] = 0u;
+        if (b >= nbk) continue;
+        const int t = b * kWave + lane;
+        cv[b] = t < cnt;
+        const int j = cv[b] ? qg[t] : 0;
+        if (cv[b]) cand[b] = CR::pack(rec[j], j);
+    }
+#pragma unroll
+    for (int b = 0; b < CH; ++b) {
+        if (b >= nbk) break;
+        nlist_bounds<PREC, NS, true>(box, pc, cand[b], cv[b], thr[b], thr1[b]);
+    }
+    nlist_homes<PREC, NS, true, LG, CH>(st, g, box, pc, hrec, kreg, homes, cand, cv, thr, thr1, nbk);
+}
+
 // One home cell (local Hilbert rank c of a box whose cells start at c_off in
-// the flattened cell arrays; rank_of and cell_lin are that box's tables).
-// QC: FP32 criterion of a cubic box, in squared quanta (raw differences
+// the flattened cell arrays; rank_of and cell_pos are that box's tables).
+// QC: a cubic box. FP32: the criterion in squared quanta (raw differences
 // against r_L^2 / quantum^2).
 //
 // With QC the home particles are split in two groups at the middle of their
 // extent along z, and every candidate is first tested against the bounding
 // box of each group: it is dropped for a group when its distance to the box
-// (in quanta, per axis the wrapped gap to the box's extent) exceeds r_L with
-// a margin of 2^-18 relative, which covers the roundings of both that bound
-// and the exact test (a few units of 2^-24 each), so a dropped candidate
-// fails the exact test for every home particle of the group. The survivors'
-// indices go, in candidate order, to a per-group queue in LDS; whenever a
-// queue holds CH blocks' worth (and once more at the end), the wave reloads
-// them from the particles' records and runs the exact test for that group's
-// home particles only. So the lists are the same entries in the same order
-// as without the reduction, while at liquid density the exact test runs
+// (in quanta) exceeds r_L with a margin of 2^-17 relative, which covers the
+// roundings of that bound (binary32 coordinates relative to the box, up to a
+// few r_L) and of the exact test, so a dropped candidate fails the exact test
+// for every home particle of the group; the FP64 path rounds its coordinates
+// to quanta for this test only and adds a few quanta to the bound. The
+// survivors' indices go, in candidate order, to a per-group queue in LDS;
+// whenever a queue holds CH blocks' worth (and once more at the end), the wave
+// reloads them from the particles' records and runs the exact test for that
+// group's home particles only. So the lists are the same entries in the same
+// order as without the reduction, while at liquid density the exact test runs
 // over about 0.7 of the (particle, block) pairs of a single reduction per
 // cell (two smaller boxes, and blocks filled across chunks), at the price of
 // a second, cheap test per candidate. rec: the particles' position records,
-// the same as the cell slots hold. queue: 2 x NlistQueue<CH>::kCap entries
-// of this wave.
+// the same as the cell slots hold.
+//
+// What bounds it (FP32, N = 256,000, 80 us per rebuild): the home particles'
+// exact tests take 50 us of it, the list stores 4 us; of the tests' vector
+// instructions the conversions, compares and bit counts run at half rate
+// (1.7 ns per wave against 1.0 ns for an integer or float add or multiply).
+// FP64 (N = 256,000): 200 us per rebuild with every candidate tested exactly,
+// 120 us with the reduction.
 // LG: log2 of the lanes per particle of the list layout when it is known at
 // compile time (the shifts and masks of the entry index fold), -1 to read it
 // from g.lanes. WIDE: the grid has at least 2 R + 2 cells along every axis
@@ -549,17 +604,17 @@ struct NlistQueue {
 // bounds of one form).
 template <int PREC, int NS, bool QC, int LG, bool WIDE>
 __device__ inline void nlist_cell_as(const State &st, const Geom &g, const BoxC &box, const PairC &pc,
-                                     const int32_t *rank_of, const int32_t *cell_lin, int64_t c_off, int c,
-                                     Ctl *ctl, const typename CellRec<PREC>::T *__restrict__ rec, int32_t *queue) {
+                                     const int32_t *rank_of, const int32_t *cell_pos, int64_t c_off, int c,
+                                     Ctl *ctl, const typename CellRec<PREC>::T *__restrict__ rec,
+                                     NlistLds<PREC, QC> &sm) {
     using CR = CellRec<PREC>;
     using T = typename CR::T;
-    constexpr bool FILT = PREC == LJMD_FP32_DS && QC;
-    constexpr int CH = NlistChunk<PREC, FILT>::CH;
+    constexpr bool FILT = QC;
+    constexpr int CH = NlistChunk<PREC, FILT>::CH, CL = NlistChunk<PREC, FILT>::CL;
     const int lane = threadIdx.x & 63;
     const T *__restrict__ cr = cell_recs<PREC>(st);
-    const int lin = cell_lin[c];
-    const int cc[3] = {lin / (box.nc[1] * box.nc[2]), (lin / box.nc[2]) % box.nc[1],
-                       lin % box.nc[2]};
+    const int pos = cell_pos[c];
+    const int cc[3] = {pos >> 20, (pos >> 10) & 1023, pos & 1023};
     // Stencil: the cells within box.reach cells of the home cell along each
     // axis (3 x 3 x 3 with cells of edge >= r_L, 5 x 5 x 5 with cells of
     // edge >= r_L / 2), or every cell of an axis that has fewer (each cell
@@ -578,12 +633,14 @@ __device__ inline void nlist_cell_as(const State &st, const Geom &g, const BoxC 
     const int nst = n3[0] * n3[1] * n3[2];
     const int home = (int)c_off + c;
     const int m = min(st.cell_count[home], g.cell_cap);
-    // Largest list radius of any pair type, with the margin of the reduction.
+    // Largest list radius of any pair type, with the margin of the reduction
+    // (FP64: its coordinates are rounded to quanta for the box test only).
     float reach = 0.0f;
     if constexpr (FILT) {
         reach = box.rl2q[0];
         if constexpr (NS == 2) reach = fmaxf(reach, fmaxf(box.rl2q[1], box.rl2q[2]));
-        reach *= 1.0f + 0x1p-18f;
+        if constexpr (PREC == LJMD_FP64) reach += 8.0f * sqrtf(reach) + 16.0f;
+        reach *= 1.0f + 0x1p-17f;
     }
     for (int h0 = 0; h0 < m; h0 += kWave) {
         const int hm = min(m - h0, kWave);
@@ -599,7 +656,8 @@ __device__ inline void nlist_cell_as(const State &st, const Geom &g, const BoxC 
         int fill[2] = {0, 0};
         if constexpr (FILT) {
             const bool act = lane < hm;
-            const uint32_t hq[3] = {(uint32_t)hrec.x, (uint32_t)hrec.y, (uint32_t)hrec.z};
+            uint32_t hq[3];
+            rec_q(hrec, box, hq);
             const uint32_t zmn = wave_min_u32(act ? hq[2] : 0xffffffffu);
             const uint32_t zmx = wave_max_u32(act ? hq[2] : 0u);
             const bool up = act && hq[2] - zmn > ((zmx - zmn) >> 1);
@@ -622,39 +680,14 @@ __device__ inline void nlist_cell_as(const State &st, const Geom &g, const BoxC 
         // candidate then lies within half a box of the home cell, and the
         // wrapped gap to a group's box is the plain signed one (glo, ghi:
         // the box's extent relative to group 0's corner).
-        int32_t glo[2][3], ghi[2][3];
+        float glo[2][3], ghi[2][3];
         for (int gi = 0; gi < 2; ++gi)
             for (int a = 0; a < 3; ++a) {
-                glo[gi][a] = (int32_t)(bmn[gi][a] - bmn[0][a]);
-                ghi[gi][a] = glo[gi][a] + (int32_t)bspan[gi][a];
+                const int32_t l = (int32_t)(bmn[gi][a] - bmn[0][a]);
+                glo[gi][a] = (float)l;
+                ghi[gi][a] = (float)(l + (int32_t)bspan[gi][a]);
             }
         int kreg = 0;
-        // FILT: test the home particles of group gi against the first cnt
-        // queued candidates (cnt <= CH blocks), reloaded from their records.
-        auto drain = [&](int gi, int cnt) {
-            T cand[CH];
-            bool cv[CH];
-            uint32_t thr[CH], thr1[CH];
-            const int nbk = (cnt + kWave - 1) / kWave;
-            const int32_t *qg = queue + gi * NlistQueue<CH>::kCap;
-#pragma unroll
-            for (int b = 0; b < CH; ++b) {
-                cv[b] = false;
-                cand[b] = T{};
-                thr[b] = thr1[b] = 0u;
-                if (b >= nbk) continue;
-                const int t = b * kWave + lane;
-                cv[b] = t < cnt;
-                const int j = cv[b] ? qg[t] : 0;
-                if (cv[b]) cand[b] = CR::pack(rec[j], j);
-            }
-#pragma unroll
-            for (int b = 0; b < CH; ++b) {
-                if (b >= nbk) break;
-                nlist_bounds<PREC, NS, QC>(box, pc, cand[b], cv[b], thr[b], thr1[b]);
-            }
-            nlist_homes<PREC, NS, QC, LG, CH>(st, g, box, pc, hrec, kreg, gmask[gi], cand, cv, thr, thr1, nbk);
-        };
         for (int s0 = 0; s0 < nst; s0 += kWave) {
         // Stencil cells s0 .. s0 + nsp - 1: lane e holds cell s0 + e, its
         // flattened index, its (capped) count and the offset of its first
@@ -663,7 +696,12 @@ __device__ inline void nlist_cell_as(const State &st, const Geom &g, const BoxC 
         int scell = 0, scnt = 0;
         if (lane < nsp) {
             const int sl = s0 + lane;
-            const int a = sl / (n3[1] * n3[2]), bb = (sl / n3[2]) % n3[1], d = sl % n3[2];
+            int a, bb, d;
+            if (n3[1] == 3 && n3[2] == 3) {  // division by constants
+                a = sl / 9, bb = sl / 3 % 3, d = sl % 3;
+            } else {
+                a = sl / (n3[1] * n3[2]), bb = (sl / n3[2]) % n3[1], d = sl % n3[2];
+            }
             int ax = cc[0] + lo[0] + a, ay = cc[1] + lo[1] + bb, az = cc[2] + lo[2] + d;
             ax += ax < 0 ? box.nc[0] : (ax >= box.nc[0] ? -box.nc[0] : 0);
             ay += ay < 0 ? box.nc[1] : (ay >= box.nc[1] ? -box.nc[1] : 0);
@@ -676,118 +714,142 @@ __device__ inline void nlist_cell_as(const State &st, const Geom &g, const BoxC 
             const int y = __shfl_up(incl, o);
             if (lane >= o) incl += y;
         }
-        const int soff = incl - scnt;
         const int ncand = __builtin_amdgcn_readlane(incl, kWave - 1);  // wave-uniform, in a scalar register
-        const int top = nsp > 32 ? 32 : 16;
-        for (int cb = 0; cb < ncand; cb += CH * kWave) {
-            // Blocks of 64 candidates this chunk holds (wave-uniform): the
-            // last chunk of a cell is usually short.
-            const int nbk = min(CH, (ncand - cb + kWave - 1) / kWave);
-            T cand[CH];
-            bool cv[CH];
+        // The cells that hold anything, in order (kept in LDS: the loops below
+        // are short of registers).
+        const unsigned long long full = __ballot(scnt > 0);
+        const int nfull = __popcll(full);
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (scnt > 0)
+            sm.cells[__builtin_amdgcn_mbcnt_hi((uint32_t)(full >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)full, 0u))] =
+                make_int2(scell, incl - scnt);
+        const bool last_part = s0 + kWave >= nst;
+        // At least one round for the last part, so that the queues drain.
+        for (int cb = 0; cb < ncand || (cb == 0 && last_part); cb += CL * kWave) {
+            // Blocks of 64 candidates this round holds (wave-uniform): the
+            // last round of a cell is usually short.
+            const int nbk = min(CL, (ncand - cb + kWave - 1) / kWave);
+            T cand[CL];
+            bool cv[CL];
+            // Candidate cb + r belongs to the last full cell whose first
+            // candidate is at or before it. Cells that start inside the round
+            // set bit (start - cb - 1); the cell of candidate r is then found
+            // by counting the bits below r (two instructions per block
+            // instead of a binary search by shuffles, which took 60 of the
+            // ~380 vector instructions a block cost).
+            if (lane < 2 * CL) sm.heads[lane] = 0u;
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const int rel = lane < nfull ? sm.cells[lane].y - cb : CL * kWave + 1;
+            if (rel > 0 && rel <= CL * kWave) atomicOr(&sm.heads[(rel - 1) >> 5], 1u << ((rel - 1) & 31));
+            uint32_t before = (uint32_t)__popcll(__ballot(rel <= 0)) - 1u;
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            __builtin_amdgcn_wave_barrier();
 #pragma unroll
-            for (int b = 0; b < CH; ++b) {
+            for (int b = 0; b < CL; ++b) {
                 cv[b] = false;
                 cand[b] = T{};
                 if (b >= nbk) continue;
                 const int t = cb + b * kWave + lane;
-                // Largest stencil cell s of this part with soff[s] <= t: a
-                // fixed 5-step (6 with more than 32 cells) binary search,
-                // every lane shuffling in every step.
-                int sel = 0;
-                for (int stp = top; stp >= 1; stp >>= 1) {
-                    const int cand_s = sel + stp;
-                    const int v = __shfl(soff, cand_s < nsp ? cand_s : nsp - 1);
-                    if (cand_s < nsp && v <= t) sel = cand_s;
-                }
-                const int cs = __shfl(scell, sel), os = __shfl(soff, sel);
+                const uint32_t w0 = sm.heads[2 * b], w1 = sm.heads[2 * b + 1];
+                const int sel = (int)__builtin_amdgcn_mbcnt_hi(w1, __builtin_amdgcn_mbcnt_lo(w0, before));
+                before += __builtin_popcount(w0) + __builtin_popcount(w1);
+                const int2 own = sm.cells[sel & (kWave - 1)];
                 cv[b] = t < ncand;
-                int e = t - os;
-                e = e < 0 ? 0 : (e >= g.cell_cap ? g.cell_cap - 1 : e);
-                const int64_t at = cv[b] ? (int64_t)cs * g.cell_cap + e : 0;
+                const uint64_t at =
+                    cv[b] ? (uint64_t)(uint32_t)own.x * (uint32_t)g.cell_cap + (uint32_t)(t - own.y) : 0u;
                 cand[b] = cr[at];
                 cv[b] = cv[b] && (unsigned)CR::index(cand[b]) < (unsigned)g.n;
             }
             if constexpr (FILT) {
                 // Queue, per group, the candidates within reach of its box.
 #pragma unroll
-                for (int b = 0; b < CH; ++b) {
+                for (int b = 0; b < CL; ++b) {
                     if (b >= nbk) break;
                     // Wide grids: the candidate's coordinates relative to
                     // group 0's box corner, as signed quanta (the direct
                     // image is the nearest one).
-                    const int32_t dx = (int32_t)((uint32_t)cand[b].x - bmn[0][0]);
-                    const int32_t dy = (int32_t)((uint32_t)cand[b].y - bmn[0][1]);
-                    const int32_t dz = (int32_t)((uint32_t)cand[b].z - bmn[0][2]);
+                    uint32_t q[3];
+                    rec_q(cand[b], box, q);
+                    const float fx = (float)(int32_t)(q[0] - bmn[0][0]);
+                    const float fy = (float)(int32_t)(q[1] - bmn[0][1]);
+                    const float fz = (float)(int32_t)(q[2] - bmn[0][2]);
                     const unsigned long long cvm = __builtin_amdgcn_ballot_w64(cv[b]);
 #pragma unroll
                     for (int gi = 0; gi < 2; ++gi) {
                         float gx, gy, gz;
                         if constexpr (WIDE) {
-                            gx = (float)max(max(glo[gi][0] - dx, dx - ghi[gi][0]), 0);
-                            gy = (float)max(max(glo[gi][1] - dy, dy - ghi[gi][1]), 0);
-                            gz = (float)max(max(glo[gi][2] - dz, dz - ghi[gi][2]), 0);
+                            // Signed distance to the box along each axis.
+                            gx = fx - __builtin_amdgcn_fmed3f(fx, glo[gi][0], ghi[gi][0]);
+                            gy = fy - __builtin_amdgcn_fmed3f(fy, glo[gi][1], ghi[gi][1]);
+                            gz = fz - __builtin_amdgcn_fmed3f(fz, glo[gi][2], ghi[gi][2]);
                         } else {
-                            gx = (float)gap_q((uint32_t)cand[b].x, bmn[gi][0], bspan[gi][0]);
-                            gy = (float)gap_q((uint32_t)cand[b].y, bmn[gi][1], bspan[gi][1]);
-                            gz = (float)gap_q((uint32_t)cand[b].z, bmn[gi][2], bspan[gi][2]);
+                            gx = (float)gap_q(q[0], bmn[gi][0], bspan[gi][0]);
+                            gy = (float)gap_q(q[1], bmn[gi][1], bspan[gi][1]);
+                            gz = (float)gap_q(q[2], bmn[gi][2], bspan[gi][2]);
                         }
                         // The ballot of the bare compare, masked with the
                         // real candidates' ballot in scalar registers.
                         const bool near = fmaf(gz, gz, fmaf(gy, gy, gx * gx)) <= greach[gi];
                         const unsigned long long km = __builtin_amdgcn_ballot_w64(near) & cvm;
-                        const uint32_t pos = __builtin_amdgcn_mbcnt_hi(
-                            (uint32_t)(km >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)km, (uint32_t)fill[gi]));
-                        if (near && cv[b]) queue[gi * NlistQueue<CH>::kCap + pos] = CR::index(cand[b]);
+                        const uint32_t at = __builtin_amdgcn_mbcnt_hi(
+                            (uint32_t)(km >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)km, 0u));
+                        if (near && cv[b]) sm.queue[gi][fill[gi] + at] = CR::index(cand[b]);
                         fill[gi] += __popcll(km);
                     }
                 }
                 __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
                 __builtin_amdgcn_wave_barrier();
-                // A queue holding CH blocks or more: test its first CH
-                // blocks, then move the rest (fewer than CH blocks) to its
-                // front.
+                // A queue holding CH blocks or more (any, after the last
+                // round): test its first CH blocks, then move the rest (at
+                // most CL blocks) to its front.
+                const bool flush = last_part && cb + CL * kWave >= ncand;
+#pragma unroll 1
                 for (int gi = 0; gi < 2; ++gi) {
-                    if (fill[gi] < CH * kWave) continue;
-                    drain(gi, CH * kWave);
-                    int32_t *qg = queue + gi * NlistQueue<CH>::kCap;
-                    const int rest = fill[gi] - CH * kWave;
-                    int32_t mv[CH];
+                    int32_t *qg = sm.queue[gi];
+                    const uint64_t gm = gi ? gmask[1] : gmask[0];
+                    int f = gi ? fill[1] : fill[0];
+                    while (f >= CH * kWave || (flush && f > 0)) {
+                        const int cnt = min(f, CH * kWave);
+                        nlist_homes_queued<PREC, NS, LG>(st, g, box, pc, hrec, kreg, gm, qg, cnt, rec);
+                        f -= cnt;
+                        if (f > 0) {
+                            int32_t mv[CL];
 #pragma unroll
-                    for (int b = 0; b < CH; ++b) {
-                        const int t = b * kWave + lane;
-                        mv[b] = t < rest ? qg[CH * kWave + t] : 0;
-                    }
-                    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
+                            for (int b = 0; b < CL; ++b) {
+                                const int t = b * kWave + lane;
+                                mv[b] = t < f ? qg[CH * kWave + t] : 0;
+                            }
+                            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                            __builtin_amdgcn_wave_barrier();
 #pragma unroll
-                    for (int b = 0; b < CH; ++b) {
-                        const int t = b * kWave + lane;
-                        if (t < rest) qg[t] = mv[b];
+                            for (int b = 0; b < CL; ++b) {
+                                const int t = b * kWave + lane;
+                                if (t < f) qg[t] = mv[b];
+                            }
+                            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                            __builtin_amdgcn_wave_barrier();
+                        }
                     }
-                    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    fill[gi] = rest;
+                    if (gi) fill[1] = f;
+                    else fill[0] = f;
                 }
             } else {
-                uint32_t thr[CH], thr1[CH];
+                static_assert(CH == CL || FILT, "one block size without the reduction");
+                uint32_t thr[CL], thr1[CL];
 #pragma unroll
-                for (int b = 0; b < CH; ++b) {
+                for (int b = 0; b < CL; ++b) {
                     thr[b] = thr1[b] = 0u;
                     if (b >= nbk) continue;
                     nlist_bounds<PREC, NS, QC>(box, pc, cand[b], cv[b], thr[b], thr1[b]);
                 }
-                nlist_homes<PREC, NS, QC, LG, CH>(st, g, box, pc, hrec, kreg, all, cand, cv, thr, thr1, nbk);
+                nlist_homes<PREC, NS, QC, LG, CL>(st, g, box, pc, hrec, kreg, all, cand, cv, thr, thr1, nbk);
             }
-        }
-        }
-        if constexpr (FILT) {
-            for (int gi = 0; gi < 2; ++gi)
-                if (fill[gi] > 0) drain(gi, fill[gi]);
-            // The next group of home particles (cells over 64) starts on
-            // empty queues; make this group's reads complete first.
+            // The next round clears the head bits: this one's reads are done.
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
             __builtin_amdgcn_wave_barrier();
+        }
         }
         if (lane < hm) {
             const int i = CR::index(hrec);
@@ -805,35 +867,34 @@ __device__ inline void nlist_cell_as(const State &st, const Geom &g, const BoxC 
 // The lists of home cell c (see nlist_cell_as).
 template <int PREC, int NS, bool QC, int LG = -1>
 __device__ inline void nlist_cell(const State &st, const Geom &g, const BoxC &box, const PairC &pc,
-                                  const int32_t *rank_of, const int32_t *cell_lin, int64_t c_off, int c,
-                                  Ctl *ctl, const typename CellRec<PREC>::T *__restrict__ rec, int32_t *queue) {
-    constexpr bool FILT = PREC == LJMD_FP32_DS && QC;
+                                  const int32_t *rank_of, const int32_t *cell_pos, int64_t c_off, int c,
+                                  Ctl *ctl, const typename CellRec<PREC>::T *__restrict__ rec,
+                                  NlistLds<PREC, QC> &sm) {
     const int w = 2 * box.reach + 2;
-    if (FILT && box.nc[0] >= w && box.nc[1] >= w && box.nc[2] >= w)
-        nlist_cell_as<PREC, NS, QC, LG, FILT>(st, g, box, pc, rank_of, cell_lin, c_off, c, ctl, rec, queue);
+    if (QC && box.nc[0] >= w && box.nc[1] >= w && box.nc[2] >= w)
+        nlist_cell_as<PREC, NS, QC, LG, QC>(st, g, box, pc, rank_of, cell_pos, c_off, c, ctl, rec, sm);
     else
-        nlist_cell_as<PREC, NS, QC, LG, false>(st, g, box, pc, rank_of, cell_lin, c_off, c, ctl, rec, queue);
+        nlist_cell_as<PREC, NS, QC, LG, false>(st, g, box, pc, rank_of, cell_pos, c_off, c, ctl, rec, sm);
 }
 
-// Per-block LDS of the reduced list build (FP32 cubic boxes only): two
-// candidate queues per wave.
-template <int PREC, bool QC>
-struct NlistStage {
-    static constexpr int kPerWave =
-        (PREC == LJMD_FP32_DS && QC) ? 2 * NlistQueue<NlistChunk<PREC, true>::CH>::kCap : 0;
-    static constexpr int kEntries = kPerWave > 0 ? kNlWaves * kPerWave : 1;
-};
+// Waves per SIMD the list build's registers are held to. One species: six
+// (80 registers). Two species: five without spills; six spill, and large boxes
+// (the per-XCD queues) run five waves anyway: 1.30 against 1.33 ms per rebuild
+// of the 4M mixture. FP64: four (96-100 registers).
+template <int PREC, int NS>
+constexpr int nlist_waves() {
+    return PREC == LJMD_FP64 ? 4 : (NS == 2 ? 5 : 6);
+}
 
 template <int PREC, int NS, bool QC, int LG = -1>
-__global__ __launch_bounds__(kNlWaves * kWave, 6) void k_nlist(State st, Geom g, BoxC box, PairC pc, int cur,
-                                                            int64_t step, int forced, float thr2) {
+__global__ __launch_bounds__(kNlWaves * kWave, (nlist_waves<PREC, NS>())) void k_nlist(
+    State st, Geom g, BoxC box, PairC pc, int cur, int64_t step, int forced, float thr2) {
     if (halted(st.ctl) || !rebuild_due(st.ctl, step, forced, thr2)) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) st.ctl->rebuilds += 1;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), W = blockDim.x >> 6;
     const int tw = gridDim.x * W;
-    using Stage = NlistStage<PREC, QC>;
-    __shared__ int32_t queue_all[Stage::kEntries];
-    int32_t *queue = queue_all + wv * Stage::kPerWave;
+    __shared__ NlistLds<PREC, QC> sm_all[kNlWaves];
+    NlistLds<PREC, QC> &sm = sm_all[wv];
     const auto *rec = records<PREC>(st, cur);
     if (box.ncell < 8 * tw) {
         // A few cells per wave: contiguous runs of Hilbert-ranked cells, each
@@ -842,7 +903,7 @@ __global__ __launch_bounds__(kNlWaves * kWave, 6) void k_nlist(State st, Geom g,
         const int per = (box.ncell + tw - 1) / tw;
         const int cbeg = gw * per, cend = min(cbeg + per, box.ncell);
         for (int c = cbeg; c < cend; ++c)
-            nlist_cell<PREC, NS, QC, LG>(st, g, box, pc, st.rank_of, st.cell_lin, 0, c, st.ctl, rec, queue);
+            nlist_cell<PREC, NS, QC, LG>(st, g, box, pc, st.rank_of, st.cell_pos, 0, c, st.ctl, rec, sm);
         return;
     }
     // Many cells per wave: each XCD (blocks are dispatched to XCD
@@ -859,7 +920,7 @@ __global__ __launch_bounds__(kNlWaves * kWave, 6) void k_nlist(State st, Geom g,
         if (lane == 0) c = lo + (int)atomicAdd(&st.ctl->nlq[q], 1u);
         c = __builtin_amdgcn_readfirstlane(c);  // wave-uniform from here on
         if (c >= hi) break;
-        nlist_cell<PREC, NS, QC, LG>(st, g, box, pc, st.rank_of, st.cell_lin, 0, c, st.ctl, rec, queue);
+        nlist_cell<PREC, NS, QC, LG>(st, g, box, pc, st.rank_of, st.cell_pos, 0, c, st.ctl, rec, sm);
     }
 }
 
@@ -915,8 +976,8 @@ __global__ __launch_bounds__(kRebuildSmallWaves * kWave) void k_rebuild_small(St
 
     // The stencil: per axis cells s0 .. s0 + n3 - 1 (wrapped), the whole axis
     // where it has fewer than three.
-    const int lin = st.cell_lin[blockIdx.x];
-    const int cc[3] = {lin / (box.nc[1] * box.nc[2]), (lin / box.nc[2]) % box.nc[1], lin % box.nc[2]};
+    const int pos = st.cell_pos[blockIdx.x];
+    const int cc[3] = {pos >> 20, (pos >> 10) & 1023, pos & 1023};
     int s0[3], n3[3];
     for (int a = 0; a < 3; ++a) {
         const bool wide = box.nc[a] >= 3;
@@ -1185,9 +1246,8 @@ __global__ __launch_bounds__(kNlWaves * kWave, 5) void k_batch_nlist(State st, G
     const int q = (int)(blockIdx.x % (unsigned)nq);
     const int64_t lo = total * q / nq, hi = total * (q + 1) / nq;
     const int lane = threadIdx.x & 63;
-    using Stage = NlistStage<LJMD_FP32_DS, true>;
-    __shared__ int32_t queue_all[Stage::kEntries];
-    int32_t *queue = queue_all + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) * Stage::kPerWave;
+    __shared__ NlistLds<LJMD_FP32_DS, true> sm_all[kNlWaves];
+    NlistLds<LJMD_FP32_DS, true> &sm = sm_all[__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))];
     const int4 *rec = records<LJMD_FP32_DS>(st, cur);
     for (;;) {
         int64_t w = 0;
@@ -1199,8 +1259,8 @@ __global__ __launch_bounds__(kNlWaves * kWave, 5) void k_batch_nlist(State st, G
         const int s = bp.wl_sys[k];
         const SysC &y = sys[s];
         const int64_t first = lds ? plan_sh[k] : bp.wl_coff[k];
-        nlist_cell<LJMD_FP32_DS, 1, true, LG>(st, g, y.box, pc, st.rank_of + y.c_off, st.cell_lin + y.c_off,
-                                              y.c_off, (int)(w - first), st.ctl + s, rec, queue);
+        nlist_cell<LJMD_FP32_DS, 1, true, LG>(st, g, y.box, pc, st.rank_of + y.c_off, st.cell_pos + y.c_off,
+                                              y.c_off, (int)(w - first), st.ctl + s, rec, sm);
     }
 }
 
@@ -1286,8 +1346,8 @@ static void nlist_launch(const Launch &L, int64_t step, int forced) {
     if (PREC == LJMD_FP32_DS && L.box->cubic && L.g->lanes == 2)
         hipLaunchKernelGGL((k_nlist<PREC, NS, PREC == LJMD_FP32_DS, 1>), dim3(nb), dim3(kNlWaves * kWave), 0,
                            L.stream, *L.st, *L.g, *L.box, *L.pc, L.cur, step, forced, L.dyn->thr2);
-    else if (PREC == LJMD_FP32_DS && L.box->cubic)
-        hipLaunchKernelGGL((k_nlist<PREC, NS, PREC == LJMD_FP32_DS>), dim3(nb), dim3(kNlWaves * kWave), 0, L.stream,
+    else if (L.box->cubic)
+        hipLaunchKernelGGL((k_nlist<PREC, NS, true>), dim3(nb), dim3(kNlWaves * kWave), 0, L.stream,
                            *L.st, *L.g, *L.box, *L.pc, L.cur, step, forced, L.dyn->thr2);
     else
         hipLaunchKernelGGL((k_nlist<PREC, NS, false>), dim3(nb), dim3(kNlWaves * kWave), 0, L.stream, *L.st,

@@ -211,27 +211,28 @@ __device__ inline void step_ds_body(const StepArgs &a, const BoxC &box, Ctl *ctl
                 const float dz = (float)(int32_t)((uint32_t)ri.z - (uint32_t)rr[u].z);
                 const float r2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
                 const int sj = rr[u].w;
-                const bool in = m + u < iters && r2 < (NS == 1 ? rc2q : q_rc2(sj));
-                if (SMALL || in) {
-                    const float ir2 = SMALL ? (in ? __builtin_amdgcn_rcpf(r2) : 0.0f) : __builtin_amdgcn_rcpf(r2);
-                    const float s2 = (NS == 1 ? sig2q : q_sig2(sj)) * ir2;
-                    const float s6 = s2 * s2 * s2;
-                    float t = (s6 * ir2) * fmaf(2.0f, s6, -1.0f);
-                    if constexpr (NS == 2) t *= q_f(sj);
-                    fx = fmaf(t, dx, fx);
-                    fy = fmaf(t, dy, fy);
-                    fz = fmaf(t, dz, fz);
-                    if constexpr (OBS) {
-                        if constexpr (NS == 1) {
-                            sa = fmaf(s6, s6, sa);
-                            sb += s6;
-                            an += SMALL ? (in ? 1 : 0) : 1;
-                        } else {
-                            const float s12 = s6 * s6;
-                            const float sh = SMALL ? (in ? t_shift(sj) : 0.0f) : t_shift(sj);
-                            sa += fmaf(t_eps4(sj), s12 - s6, -sh);
-                            sb += t_eps24(sj) * fmaf(2.0f, s12, -s6);
-                        }
+                bool in = true;
+                if constexpr (SMALL)
+                    in = m + u < iters && r2 < (NS == 1 ? rc2q : q_rc2(sj));
+                else if (!(m + u < iters && r2 < (NS == 1 ? rc2q : q_rc2(sj))))
+                    continue;
+                const float ir2 = in ? __builtin_amdgcn_rcpf(r2) : 0.0f;
+                const float s2 = (NS == 1 ? sig2q : q_sig2(sj)) * ir2;
+                const float s6 = s2 * s2 * s2;
+                float t = (s6 * ir2) * fmaf(2.0f, s6, -1.0f);
+                if constexpr (NS == 2) t *= q_f(sj);
+                fx = fmaf(t, dx, fx);
+                fy = fmaf(t, dy, fy);
+                fz = fmaf(t, dz, fz);
+                if constexpr (OBS) {
+                    if constexpr (NS == 1) {
+                        sa = fmaf(s6, s6, sa);
+                        sb += s6;
+                        an += in ? 1 : 0;
+                    } else {
+                        const float s12 = s6 * s6;
+                        sa += fmaf(t_eps4(sj), s12 - s6, in ? -t_shift(sj) : 0.0f);
+                        sb += t_eps24(sj) * fmaf(2.0f, s12, -s6);
                     }
                 }
             }

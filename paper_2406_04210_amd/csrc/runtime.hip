@@ -193,6 +193,12 @@ void grid_dims(const ljmd_params *p, int nc[3]) {
     if (dim_of(p) == 2) nc[2] = 1;
 }
 
+// Grid position of the cell with linear index k, packed (at most 1024 cells
+// per axis).
+int32_t cell_position(int k, const int nc[3]) {
+    return (k / (nc[1] * nc[2])) << 20 | (k / nc[2] % nc[1]) << 10 | k % nc[2];
+}
+
 struct Plan {
     int64_t npad;
     int32_t cap, cell_cap, lanes;
@@ -813,7 +819,7 @@ void bind_state(State &s, const Plan &pl, uint8_t *b, int prec) {
     s.cell_rec = (void *)(b + pl.off_cmem);
     s.cell_start = (int32_t *)(b + pl.off_cstart);
     s.rank_of = (int32_t *)(b + pl.off_rank);
-    s.cell_lin = (int32_t *)(b + pl.off_lin);
+    s.cell_pos = (int32_t *)(b + pl.off_lin);
     s.scratch = b + pl.off_scratch;
     s.partials = (double *)(b + pl.off_part);
     s.rebuilt = (int32_t *)(b + pl.off_rebuilt);
@@ -1097,13 +1103,13 @@ int ljmd_create(const ljmd_params *p, void *ws, size_t bytes, void *stream, ljmd
     State &s = c->st;
     bind_state(s, pl, b, p->precision);
 
-    std::vector<int32_t> rank(pl.ncell), lin(pl.ncell);
+    std::vector<int32_t> rank(pl.ncell), pos(pl.ncell);
     ljmd_hilbert_ranks(pl.nc[0], pl.nc[1], pl.nc[2], rank.data());
-    for (int k = 0; k < pl.ncell; ++k) lin[rank[k]] = k;
+    for (int k = 0; k < pl.ncell; ++k) pos[rank[k]] = cell_position(k, pl.nc);
     hipError_t e = hipMemcpyAsync(s.rank_of, rank.data(), sizeof(int32_t) * pl.ncell,
                                   hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(s.cell_lin, lin.data(), sizeof(int32_t) * pl.ncell, hipMemcpyHostToDevice,
+        e = hipMemcpyAsync(s.cell_pos, pos.data(), sizeof(int32_t) * pl.ncell, hipMemcpyHostToDevice,
                            c->stream);
     if (e == hipSuccess) e = hipMemsetAsync(s.cell_count, 0, sizeof(int32_t) * pl.ncell, c->stream);
     if (e == hipSuccess) e = hipMemsetAsync(s.ctl, 0, sizeof(Ctl), c->stream);
@@ -1864,19 +1870,19 @@ int ljmd_batch_create(const ljmd_params *shared, const ljmd_system *sys, int32_t
     b->bp.wl_coff = (int64_t *)(base + b->bl.off_wlcoff);
     b->bp.wl_count = (int32_t *)(base + b->bl.off_wlcnt);
     // Tables: concatenated Hilbert ranks and their inverses, systems, slot groups.
-    std::vector<int32_t> rank(b->bg.ncell), lin(b->bg.ncell);
+    std::vector<int32_t> rank(b->bg.ncell), pos(b->bg.ncell);
     for (int k = 0; k < nsys; ++k) {
         const SysC &y = b->bg.sys[k];
         const std::vector<int32_t> &rk = b->bg.rank[k];
         for (int c = 0; c < y.box.ncell; ++c) {
             rank[y.c_off + c] = rk[c];
-            lin[y.c_off + rk[c]] = c;
+            pos[y.c_off + rk[c]] = cell_position(c, y.box.nc);
         }
     }
     hipError_t e = hipMemcpyAsync(b->st.rank_of, rank.data(), sizeof(int32_t) * rank.size(), hipMemcpyHostToDevice,
                                   b->stream);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(b->st.cell_lin, lin.data(), sizeof(int32_t) * lin.size(), hipMemcpyHostToDevice, b->stream);
+        e = hipMemcpyAsync(b->st.cell_pos, pos.data(), sizeof(int32_t) * pos.size(), hipMemcpyHostToDevice, b->stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(b->sys, b->bg.sys.data(), sizeof(SysC) * nsys, hipMemcpyHostToDevice, b->stream);
     if (e == hipSuccess)

@@ -62,3 +62,28 @@ def test_small_rebuild_refuses_an_overfull_cell(ljmd, prec):
     with pytest.raises(ljmd.LJMDError) as err:
         s.set_state(x, np.zeros_like(x), np.zeros(len(x), dtype=np.int32))
     assert err.value.code == -8                       # LJMD_ECELL
+
+
+@pytest.mark.parametrize("prec", [FP64, FP32_DS])
+@pytest.mark.parametrize("cells,two", [(3, False), (5, True)])
+def test_reduced_build_with_crowded_cells(ljmd, prec, cells, two):
+    # Just above the one-launch size, a dilute gas with a long cutoff: hundreds
+    # of particles per cell (several batches of home particles, queues that
+    # fill and are moved up many times), with 3 cells per axis (wrapped gap to
+    # the groups' boxes) and 5 (signed gap).
+    n, L = 12500, 60.0
+    p = W.binary_mixture_params() if two else W.single_species_params()
+    p.rcut[:] = L / cells / 1.001 - p.skin
+    rng = np.random.default_rng(40 + cells)
+    x = rng.uniform(0.0, L, size=(n, 3))
+    sp = (rng.uniform(size=n) < 0.2).astype(np.int32) if two else np.zeros(n, dtype=np.int32)
+    s = ljmd.System(n, (L, L, L), p, precision=prec)
+    s.set_state(x, np.zeros_like(x), sp)
+    cnt, ids = s.neighbors(cap=2304)
+    s.sync()
+    cnt, ids = cnt.cpu().numpy(), ids.cpu().numpy()
+    oc, on = oracle.build_lists(x, sp, (L, L, L), p, mode=0 if prec == FP64 else 1, cap=2304)
+    assert 64 < oc.max() <= 2304
+    assert np.array_equal(cnt, oc)
+    for i in rng.choice(n, 1500, replace=False):
+        assert np.array_equal(np.sort(ids[i, : cnt[i]]), np.sort(on[i, : oc[i]])), i
