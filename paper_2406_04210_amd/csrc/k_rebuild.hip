@@ -14,6 +14,8 @@
 // build exceeded half the skin -- paper Sec. 5: more movement, more list
 // updates). The decision reads one control word written by the previous
 // step's kernel, so no host synchronisation is needed per step.
+#include <algorithm>
+
 #include "batch.h"
 #include "internal.h"
 
@@ -361,17 +363,17 @@ struct NlistChunk {
     static constexpr int CL = PREC == LJMD_FP64 ? 4 : (FILT ? 5 : 8);
 };
 
-// Waves per list-build block, and blocks per compute unit: with up to
-// 8 cells per wave of a grid of kNlBlocksPerCu blocks per compute unit,
-// each wave takes a contiguous run of cells (measured at N = 256,000: one
-// cell per wave over 12 blocks per compute unit, 52.3 ms per 1000 steps,
-// against 54.8 ms with three cells per wave over 5); larger grids of cells
-// go through the per-XCD queues with kNlQueueBlocksPerCu blocks per compute
-// unit, the five waves per SIMD that fit at once (the 4M mixture 3.99e9 ->
-// 4.01e9 and the 512-replica batch 4.22e9 -> 4.33e9 particle-steps/s
-// against 12).
+// Waves per list-build block. A wave builds the lists of one cell and ends;
+// the dispatcher refills its place. Against two to eight cells per wave on a
+// grid of twelve blocks per compute unit that leaves no round of waves half
+// full: per step at 270,000 / 360,000 / 600,000 / 1,000,000 particles 30.0 ->
+// 23.0 / 31.6 -> 26.6 / 41.6 -> 36.0 / 65.5 -> 55.4 us of rebuild launches.
+// Against queues of cells (one per XCD) that five blocks per compute unit draw
+// from, 4,000,000 particles take 195 against 219 us a step; two species of
+// that number 264 against 254 (2,600,000: 176 / 193) and FP64 at 2,500,000 184
+// against 172 (1,000,000: 82 / 99), so these keep the queues for large boxes.
 constexpr int kNlWaves = 4;
-constexpr int kNlBlocksPerCu = 12;
+constexpr int kNlQueueCellsPerCu = 384;  // two species, FP64: queues from this many cells per compute unit on
 constexpr int kNlQueueBlocksPerCu = 5;
 
 __device__ inline int lane_read(int v, int p) { return __builtin_amdgcn_readlane(v, p); }
@@ -896,33 +898,25 @@ __global__ __launch_bounds__(kNlWaves * kWave, (nlist_waves<PREC, NS>())) void k
     if (halted(st.ctl) || !rebuild_due(st.ctl, step, forced, thr2)) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) st.ctl->rebuilds += 1;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), W = blockDim.x >> 6;
-    const int tw = gridDim.x * W;
     __shared__ NlistLds<PREC, QC> sm_all[kNlWaves];
     NlistLds<PREC, QC> &sm = sm_all[wv];
     const auto *rec = records<PREC>(st, cur);
-    if (box.ncell < 8 * tw) {
-        // A few cells per wave: contiguous runs of Hilbert-ranked cells, each
-        // XCD one contiguous share of the box.
+    if ((PREC != LJMD_FP64 && NS == 1) || (int64_t)box.ncell <= (int64_t)gridDim.x * W) {
+        // A cell, or half of one, per wave: Hilbert-ranked cells, each XCD one
+        // contiguous share of the box.
         const int gw = xcd_remap(blockIdx.x, gridDim.x) * W + wv;
-        if (QC && halves) {
-            if (gw < 2 * box.ncell)
-                nlist_cell<PREC, NS, QC, LG>(st, g, box, pc, st.rank_of, st.cell_pos, 0, gw >> 1, st.ctl, rec, sm, gw & 1);
-            return;
-        }
-        const int per = (box.ncell + tw - 1) / tw;
-        const int cbeg = gw * per, cend = min(cbeg + per, box.ncell);
-        for (int c = cbeg; c < cend; ++c)
-            nlist_cell<PREC, NS, QC, LG>(st, g, box, pc, st.rank_of, st.cell_pos, 0, c, st.ctl, rec, sm, -1);
+        const int c = QC && halves ? gw >> 1 : gw;
+        if (c < box.ncell)
+            nlist_cell<PREC, NS, QC, LG>(st, g, box, pc, st.rank_of, st.cell_pos, 0, c, st.ctl, rec, sm,
+                                         QC && halves ? gw & 1 : -1);
         return;
     }
-    // Many cells per wave: each XCD (blocks are dispatched to XCD
-    // blockIdx % 8) owns one contiguous share of the cells and its waves take
-    // the next cell of that share from a queue, since cells differ in
-    // occupancy. With fewer than 8 blocks, each block owns a share. Every
-    // wave leaves once its share is used up.
-    const int nq = gridDim.x < 8 ? (int)gridDim.x : 8;
-    const int q = (int)(blockIdx.x % (unsigned)nq);
-    const int lo = (int)((int64_t)box.ncell * q / nq), hi = (int)((int64_t)box.ncell * (q + 1) / nq);
+    // Queues: each XCD (blocks are dispatched to XCD blockIdx % 8) owns one
+    // contiguous share of the cells and its waves take the next cell of that
+    // share, since cells differ in occupancy. Every wave leaves once its share
+    // is used up. (The grid has eight blocks at least.)
+    const int q = (int)(blockIdx.x % 8u);
+    const int lo = (int)((int64_t)box.ncell * q / 8), hi = (int)((int64_t)box.ncell * (q + 1) / 8);
     const int lane = threadIdx.x & 63;
     for (;;) {
         int c = 0;
@@ -1353,10 +1347,8 @@ static void nlist_launch(const Launch &L, int64_t step, int forced) {
     // difference, at 100,000 30.9 -> 31.4.
     const int halves = L.box->cubic && (int64_t)L.box->ncell <= (int64_t)8 * ncu ? 1 : 0;
     const unsigned need = blocks_for((int64_t)L.box->ncell * (halves ? 2 : 1), kNlWaves);
-    // The kernel takes the queue path when the cells outnumber 8 per wave.
-    const bool queued = (int64_t)L.box->ncell >= (int64_t)8 * kNlWaves * kNlBlocksPerCu * ncu;
-    const unsigned cap = ncu * (queued ? kNlQueueBlocksPerCu : kNlBlocksPerCu);
-    const unsigned nb = need < cap ? (need > 0 ? need : 1u) : cap;
+    const bool queued = (PREC == LJMD_FP64 || NS == 2) && (int64_t)L.box->ncell >= (int64_t)kNlQueueCellsPerCu * ncu;
+    const unsigned nb = queued ? std::max(8u, ncu * kNlQueueBlocksPerCu) : need;
     // The common layout of the single-precision force pass (two lanes per
     // particle) has its own instantiation with the entry index folded.
     if (PREC == LJMD_FP32_DS && L.box->cubic && L.g->lanes == 2)
