@@ -432,6 +432,15 @@ __global__ __launch_bounds__(kBlockSmall) void k_step_ds_small(StepArgs a) {
                                                                  a.st.rebuilt + a.slot);
 }
 
+// The form for large boxes in blocks of 256 threads (see fine_blocks); eight
+// waves per SIMD but for the thermostat, whose form would spill.
+template <int NS, bool OBS, bool TH, bool PLAIN>
+__global__ __launch_bounds__(kBlockSmall, (TH ? 4 : 8)) void k_step_ds_fine(StepArgs a) {
+    step_ds_body<NS, 2, true, OBS, TH, PLAIN, kBlockSmall>(a, a.box, a.st.ctl, xcd_remap(blockIdx.x, gridDim.x), a.g.n,
+                                                           0, a.box.ncell, blockIdx.x, gridDim.x,
+                                                           a.st.rebuilt + a.slot);
+}
+
 // A batch of independent one-species cubic systems, each over its own run of
 // blocks (particle ranges padded to whole blocks): the block finds its
 // system, then runs the same body with that system's box and control words.
@@ -697,6 +706,28 @@ static StepArgs make_args(const Launch &L, int64_t step, int forced, int mode, i
     return a;
 }
 
+// Whether the step kernel for large boxes runs in blocks of 256 threads
+// (quarters) instead of 1024. Two blocks of 1024 fit a compute unit, so their
+// kernel takes as long as the most loaded unit: 18.5 us with one block for
+// each, 29.5 with two, 40 with three, 50 with four, whatever n in between.
+// Quarters even that out, at a tenth more time for the same load (neighbouring
+// particles in one block share its compute unit's cache). 1024 against 256
+// threads: 68,000 particles 18.7 / 15.0 us, 90,000 18.4 / 15.9, 100,000 18.6 /
+// 19.2, 133,000 28.2 / 22.8, 160,000 29.3 / 23.9, 200,000 29.2 / 28.2, 256,000
+// 30.0 / 31.6, 270,000 39.1 / 34.5, 320,000 40.3 / 38.2, 360,000 40.4 / 41.7,
+// 400,000 50.4 / 46.6; from 600,000 on (76.1 / 80.3) the blocks that follow
+// the first round even it out.
+// The thermostat's kernel holds 84 registers, more than two blocks of 1024
+// leave room for: it always takes quarters (100,000 particles 21.0 / 20.6,
+// 256,000 37.2 / 35.1, 1,000,000 158.8 / 137.8).
+static bool fine_blocks(const Geom &g, bool th) {
+    if (th) return true;
+    const int64_t ncu = g.ncu > 0 ? g.ncu : 256;
+    const int64_t whole = (g.n + kBlock / 2 - 1) / (kBlock / 2), quarters = (g.n + kBlockSmall / 2 - 1) / (kBlockSmall / 2);
+    const int64_t load = (whole + ncu - 1) / ncu, load4 = (quarters + ncu - 1) / ncu;
+    return load <= 4 && 11 * load4 < 40 * load;
+}
+
 hipError_t launch_step(const Launch &L, int64_t step, int forced, int mode, int slot) {
     if (L.g->all_pairs) return launch_allpairs_step(L, step, mode, slot);
     StepArgs a = make_args(L, step, forced, mode, slot);
@@ -715,24 +746,30 @@ hipError_t launch_step(const Launch &L, int64_t step, int forced, int mode, int 
     // this one; at 100,000 18.6 against 19.4 us, at 256,000 30.1 against 32.1.
     const bool few_waves = L.g->n <= (int64_t)256 * (L.g->ncu > 0 ? L.g->ncu : 256);
     const bool small = quanta && L.g->lanes == 2 && few_waves;
-    if (small) {
+    if (small || (quanta && L.g->lanes == 2 && fine_blocks(*L.g, th))) {
         const dim3 gs((unsigned)L.g->max_blocks), bs(kBlockSmall);  // every row of partials is written
-#define STEP_SMALL(NS, OB)                                                           \
+#define STEP_256(K, NS, OB)                                                          \
     do {                                                                             \
         if (th && plain)                                                             \
-            launch_k(L, k_step_ds_small<NS, OB, true, true>, gs, bs, a);             \
+            launch_k(L, K<NS, OB, true, true>, gs, bs, a);                           \
         else if (th)                                                                 \
-            launch_k(L, k_step_ds_small<NS, OB, true, false>, gs, bs, a);            \
+            launch_k(L, K<NS, OB, true, false>, gs, bs, a);                          \
         else if (plain)                                                              \
-            launch_k(L, k_step_ds_small<NS, OB, false, true>, gs, bs, a);            \
+            launch_k(L, K<NS, OB, false, true>, gs, bs, a);                          \
         else                                                                         \
-            launch_k(L, k_step_ds_small<NS, OB, false, false>, gs, bs, a);           \
+            launch_k(L, K<NS, OB, false, false>, gs, bs, a);                         \
     } while (0)
-        if (two && obs) STEP_SMALL(2, true);
-        else if (two) STEP_SMALL(2, false);
-        else if (obs) STEP_SMALL(1, true);
-        else STEP_SMALL(1, false);
-#undef STEP_SMALL
+#define STEP_256_OBS(K)                      \
+    do {                                     \
+        if (two && obs) STEP_256(K, 2, true);  \
+        else if (two) STEP_256(K, 2, false);   \
+        else if (obs) STEP_256(K, 1, true);    \
+        else STEP_256(K, 1, false);            \
+    } while (0)
+        if (small) STEP_256_OBS(k_step_ds_small);
+        else STEP_256_OBS(k_step_ds_fine);
+#undef STEP_256_OBS
+#undef STEP_256
         return hipGetLastError();
     }
     // FP64, by the same rule (four waves per SIMD then): step kernel at 2,000 /

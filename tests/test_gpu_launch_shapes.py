@@ -1,10 +1,19 @@
-"""List build of a box of more cells than twelve blocks of four waves per compute
-unit hold (256 compute units): a wave per cell, lists against the oracle's.
+"""Launch shapes of boxes above 65,536 particles: the step kernel in blocks of
+256 or of 1024 threads, by how evenly either loads the compute units, and the
+list build with a wave per cell, on both sides of each line (256 compute
+units).
+
+Expected values: the same box as a batch of one, which always runs in blocks of
+1024 and adds every sum in the same order, so forces and observables are equal
+bit for bit; the oracle's forces for two species (tolerance of
+test_gpu_parity.py); four lanes per particle for the thermostat; the oracle's
+lists.
 """
 import numpy as np
 import pytest
 
 import oracle
+from force_metrics import bound_key, force_errors, reference, report, tie_allowance
 from paper_2406_04210_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
@@ -24,6 +33,51 @@ def disordered(n):
     w = W.thermostat_fluid(n, seed_index=3)
     rng = np.random.default_rng(n)
     return w, (w.x + 0.03 * rng.standard_normal(w.x.shape)) % w.box, rng
+
+
+@pytest.mark.parametrize("n", [65537, 98304, 98305, 131073, 229376, 229377, 262145, 327680, 327681])
+def test_step_blocks_repeat_a_batch_of_one(ljmd, n):
+    w, x, _ = disordered(n)
+    s = ljmd.System(n, w.box, w.params, precision=FP32_DS)
+    s.set_state(x, w.v, w.species)
+    b = ljmd.Batch([n], [w.box[0]], w.params)
+    b.set_state(x, w.v, w.species)
+    assert np.array_equal(b.forces().cpu().numpy(), s.forces().cpu().numpy())
+    obs = s.run(3).cpu().numpy()
+    assert np.array_equal(b.run(3, observe=True).cpu().numpy()[0, :6], obs[-1, :6])
+    s.run(2, observe=False)
+    b.run(2)
+    assert np.array_equal(b.forces().cpu().numpy(), s.forces().cpu().numpy())
+
+
+@pytest.mark.parametrize("n", [131073])
+def test_step_blocks_two_species(ljmd, n):
+    w, x, rng = disordered(n)
+    p = W.binary_mixture_params()
+    sp = (rng.uniform(size=n) < 0.2).astype(np.int32)
+    s = ljmd.System(n, w.box, p, precision=FP32_DS)
+    s.set_state(x, w.v, sp)
+    ref, _, _, A = reference(x, sp, w.box, p, FP32_DS)
+    m = report(f"step blocks n={n}", force_errors(s.forces().cpu().numpy(), ref, A,
+                                                  tie_allowance(x, sp, w.box, p, FP32_DS)))
+    assert m[bound_key(FP32_DS)] <= 1e-5, m
+
+
+@pytest.mark.parametrize("n", [65537, 100001])
+def test_step_blocks_thermostat(ljmd, n):
+    w, x, _ = disordered(n)
+    out = []
+    for lanes in (2, 4):
+        s = ljmd.System(n, w.box, w.params, precision=FP32_DS, lanes=lanes)
+        s.set_thermostat(1.0, 20.0, 7)
+        s.set_state(x, w.v, w.species)
+        f = s.forces().cpu().numpy()
+        s.run(3, observe=False)
+        out.append(s.get_state()[1].cpu().numpy())
+    # Both draw the same collisions; a step adds at most a force error of 1e-5
+    # of the largest force on either side, times dt / m.
+    tol = 3 * 2 * 1e-5 * np.abs(f).max() * w.params.dt / min(w.params.mass)
+    assert np.abs(out[0] - out[1]).max() <= tol
 
 
 def test_list_build_of_a_wave_per_cell(ljmd):
