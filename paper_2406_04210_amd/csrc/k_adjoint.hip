@@ -107,10 +107,20 @@ struct AdjArgs {
     double mass[2];
 };
 
+// Threads per block of the pair passes, which write one row of sums a block.
+// Blocks of 1024 load the compute units unevenly (two fit one, fewer with
+// FP64's registers): a forces call with its gradient at 32,000 / 100,000 /
+// 256,000 particles 379 -> 326 / 389 -> 354 / 475 -> 456 us, FP64 at 200,000
+// 559 -> 513. Eight or sixteen lanes per particle keep 1024: there is room for
+// a row per 64 particles.
+constexpr int kAdjBlock = 256;
+static int adjoint_threads(const Geom &g) { return g.lanes <= 4 ? kAdjBlock : kBlock; }
+
 // Six FP64 sums of one block into row `blk` of the partials (stride kNP):
 // row = (init ? 0 : row) + weight * sums.
+template <int BS>
 __device__ inline void block_rows6(const double (&v)[6], double *row, double weight, int init) {
-    constexpr int WPB = kBlock / kWave;
+    constexpr int WPB = BS / kWave;
     __shared__ double red[WPB][6];
     double s[6];
 #pragma unroll
@@ -148,9 +158,9 @@ __device__ inline void add_theta(Theta &th, int t, double ge, double gs) {
     }
 }
 
-template <int PREC, int NS, int MODE>
-__global__ __launch_bounds__(kBlock) void k_adjoint_pairs(AdjArgs a) {
-    constexpr int WPB = kBlock / kWave;
+template <int PREC, int NS, int MODE, int BS>
+__global__ __launch_bounds__(BS) void k_adjoint_pairs(AdjArgs a) {
+    constexpr int WPB = BS / kWave;
     const State &st = a.st;
     const int lanes = a.g.lanes;
     const int lg = lanes >= 16 ? 4 : (lanes >= 8 ? 3 : (lanes >= 4 ? 2 : (lanes >= 2 ? 1 : 0)));
@@ -337,7 +347,7 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_pairs(AdjArgs a) {
         if (a.next) fold_disp(st.ctl, a.next_step, a.thr2, dnext);
     }
     const double v6[6] = {th.e0, th.e1, th.e2, th.s0, th.s1, th.s2};
-    block_rows6(v6, a.rows + (size_t)blk * kNP, a.rows_weight, a.rows_init);
+    block_rows6<BS>(v6, a.rows + (size_t)blk * kNP, a.rows_weight, a.rows_init);
 }
 
 // Clears the cell counters after a rebuild of `step`: the list passes of the
@@ -470,16 +480,23 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_vec(VecArgs v) {
 
 // ------------------------------------------------------------------------
 static int adjoint_blocks(const Geom &g) {
-    const int per_block = (kBlock / kWave) * (kWave / g.lanes);
+    const int per_block = adjoint_threads(g) / g.lanes;
     return (int)((g.n + per_block - 1) / per_block);
 }
 
+template <int PREC, int NS, int BS>
+static void pairs_launch_as(int mode, dim3 grid, hipStream_t s, const AdjArgs &aa) {
+    if (mode == kAdjVjp)
+        hipLaunchKernelGGL((k_adjoint_pairs<PREC, NS, kAdjVjp, BS>), grid, dim3(BS), 0, s, aa);
+    else
+        hipLaunchKernelGGL((k_adjoint_pairs<PREC, NS, kAdjEnergy, BS>), grid, dim3(BS), 0, s, aa);
+}
 template <int PREC, int NS>
 static void pairs_launch(int mode, dim3 grid, hipStream_t s, const AdjArgs &aa) {
-    if (mode == kAdjVjp)
-        hipLaunchKernelGGL((k_adjoint_pairs<PREC, NS, kAdjVjp>), grid, dim3(kBlock), 0, s, aa);
+    if (adjoint_threads(aa.g) == kAdjBlock)
+        pairs_launch_as<PREC, NS, kAdjBlock>(mode, grid, s, aa);
     else
-        hipLaunchKernelGGL((k_adjoint_pairs<PREC, NS, kAdjEnergy>), grid, dim3(kBlock), 0, s, aa);
+        pairs_launch_as<PREC, NS, kBlock>(mode, grid, s, aa);
 }
 
 static AdjArgs pair_args(const Launch &L, const void *gvec, double4 *gx, double weight);

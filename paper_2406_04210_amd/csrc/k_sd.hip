@@ -19,9 +19,16 @@ struct SdArgs {
     int iter;
 };
 
+// Threads per block of the force pass: half of a step kernel's, which loads the
+// compute units more evenly. 50 iterations at 32,000 / 100,000 / 150,000 /
+// 256,000 particles 2528 -> 2194 / 3068 -> 2956 / 4028 -> 3628 / 4912 -> 4889
+// us, FP64 at 200,000 8090 -> 7153; with 256 threads 2126 / 3127 / 3718 / 5200
+// and 7226.
+constexpr int kSdBlock = 512;
+
 // Block maximum of |F| (non-negative doubles order like their bit patterns).
 __device__ inline void block_max_u64(unsigned long long v, unsigned long long *dst) {
-    __shared__ unsigned long long red[kBlock / kWave];
+    __shared__ unsigned long long red[kSdBlock / kWave];
     for (int o = 32; o > 0; o >>= 1) {
         const unsigned long long y = __shfl_xor(v, o);
         v = y > v ? y : v;
@@ -35,13 +42,13 @@ __device__ inline void block_max_u64(unsigned long long v, unsigned long long *d
 }
 
 template <int PREC, int NS>
-__global__ __launch_bounds__(kBlock) void k_sd_force(SdArgs sa) {
+__global__ __launch_bounds__(kSdBlock) void k_sd_force(SdArgs sa) {
     const StepArgs &a = sa.s;
     const State &st = a.st;
     const int lanes = a.g.lanes;
     const int lg = lanes >= 16 ? 4 : (lanes >= 8 ? 3 : (lanes >= 4 ? 2 : (lanes >= 2 ? 1 : 0)));
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int64_t chunk = (int64_t)xcd_remap(blockIdx.x, gridDim.x) * (kBlock / kWave) + wv;
+    const int64_t chunk = (int64_t)xcd_remap(blockIdx.x, gridDim.x) * (kSdBlock / kWave) + wv;
     const int l = lane & (lanes - 1);
     const int64_t i = (chunk << (6 - lg)) + (lane >> lg);
     const bool valid = i < a.g.n;
@@ -271,21 +278,21 @@ hipError_t launch_sd(const Launch &L, int64_t step, int forced, int iter, double
     sa.delta = delta;
     sa.fmax_out = fmax_out;
     sa.iter = iter;
-    const int per_block = (kBlock / kWave) * (kWave / L.g->lanes);
-    const dim3 gf((unsigned)((L.g->n + per_block - 1) / per_block)), b(kBlock);
+    const int per_block = (kSdBlock / kWave) * (kWave / L.g->lanes);
+    const dim3 gf((unsigned)((L.g->n + per_block - 1) / per_block)), bf(kSdBlock), b(kBlock);
     const dim3 gm((unsigned)((L.g->n + kBlock - 1) / kBlock));
     const bool two = L.g->nspecies == 2;
     if (L.g->prec == LJMD_FP64) {
         if (two)
-            hipLaunchKernelGGL((k_sd_force<LJMD_FP64, 2>), gf, b, 0, L.stream, sa);
+            hipLaunchKernelGGL((k_sd_force<LJMD_FP64, 2>), gf, bf, 0, L.stream, sa);
         else
-            hipLaunchKernelGGL((k_sd_force<LJMD_FP64, 1>), gf, b, 0, L.stream, sa);
+            hipLaunchKernelGGL((k_sd_force<LJMD_FP64, 1>), gf, bf, 0, L.stream, sa);
         hipLaunchKernelGGL(k_sd_move<LJMD_FP64>, gm, b, 0, L.stream, sa);
     } else {
         if (two)
-            hipLaunchKernelGGL((k_sd_force<LJMD_FP32_DS, 2>), gf, b, 0, L.stream, sa);
+            hipLaunchKernelGGL((k_sd_force<LJMD_FP32_DS, 2>), gf, bf, 0, L.stream, sa);
         else
-            hipLaunchKernelGGL((k_sd_force<LJMD_FP32_DS, 1>), gf, b, 0, L.stream, sa);
+            hipLaunchKernelGGL((k_sd_force<LJMD_FP32_DS, 1>), gf, bf, 0, L.stream, sa);
         if (L.g->prec == LJMD_FP32)
             hipLaunchKernelGGL((k_sd_move<LJMD_FP32_DS, true>), gm, b, 0, L.stream, sa);
         else

@@ -1,4 +1,4 @@
-"""Launch shapes of boxes above 65,536 particles: the step kernel in blocks of
+"""Launch shapes above 65,536 particles: the step kernel in blocks of
 256 or of 1024 threads, by how evenly either loads the compute units, and the
 list build with a wave per cell, on both sides of each line (256 compute
 units).
@@ -93,3 +93,34 @@ def test_list_build_of_a_wave_per_cell(ljmd):
     k = np.arange(192)[None, :] < cnt[:, None]
     big = np.int64(n)
     assert np.array_equal(np.sort(np.where(k, ids, big), 1), np.sort(np.where(k, on, big), 1))
+
+
+@pytest.mark.parametrize("lanes", [1, 2, 4, 8, 16])
+@pytest.mark.parametrize("n", [513, 1024])
+def test_pair_passes_by_lanes(ljmd, n, lanes):
+    """Force adjoint, reverse sweep and steepest descent at every number of
+    lanes per particle (their blocks follow it), FP64: against the oracle's
+    adjoint and against the default four lanes. Sums of about 80 terms in
+    another order: 1e-12 of the largest value, and 1e-10 after several steps."""
+    w, x, rng = disordered(n)
+    g = rng.standard_normal((n, 3))
+
+    def passes(k):
+        s = ljmd.System(n, w.box, w.params, precision=0, lanes=k)
+        s.set_state(x, w.v, w.species)
+        gx, gth = (t.cpu().numpy() for t in s.force_vjp(g))
+        s.vv_forward(4, 2)
+        back = [t.cpu().numpy() for t in s.vv_backward(g, 0.1 * g)]
+        s.set_state(x, w.v, w.species)
+        fm = s.minimize_sd(4).cpu().numpy()
+        return gx, gth, back, fm, s.get_state()[0].cpu().numpy()
+
+    gx, gth, back, fm, xr = passes(lanes)
+    ox, ge, gs = oracle.force_vjp(x, w.species, w.box, w.params, g)
+    assert np.abs(gx - ox).max() <= 1e-12 * np.abs(ox).max()
+    assert abs(gth[0] - ge[0]) <= 1e-12 * np.abs(ox).max() * n and abs(gth[3] - gs[0]) <= 1e-12 * np.abs(ox).max() * n
+    _, _, back4, fm4, xr4 = passes(4)
+    for a, b in zip(back, back4):
+        assert np.abs(a - b).max() <= 1e-10 * max(1.0, np.abs(b).max())
+    assert np.abs(fm - fm4).max() <= 1e-10 * fm4.max()
+    assert np.abs(xr - xr4).max() <= 1e-10 * w.box[0]
