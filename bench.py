@@ -35,9 +35,9 @@ HBM_PEAK_GBS = 8000.0
 # 512 MiB copy reads), valid only for the kernel sources they were taken on.
 STEP_KERNEL_SOURCES = ("k_step.hip", "step_common.h", "internal.h")
 STEP_KERNEL_TRAFFIC = {
-    "sources_sha256": "25fed7b0c7dd77b0ef3176e23e4fc6ca21da4fd1965334f8721c28c6047599e4",
-    "fetch_bytes": 2.0 * 53446 * 1024,
-    "write_bytes": 1.0 * 16035 * 1024,
+    "sources_sha256": "aa39f45e67b6d64d713dfa89f76c56aad8c2859c3c19b0569d4af8c23d7ad9ee",
+    "fetch_bytes": 2.0 * 53431 * 1024,
+    "write_bytes": 1.0 * 16128 * 1024,
 }
 
 

@@ -9,8 +9,9 @@
 // reads every candidate with one contiguous 16-byte (FP32) or 32-byte (FP64)
 // load instead of an index load followed by a dependent gather.
 //
-// bin, canon and nlist are launched every step and return at once unless
-// the list is due (host-forced, or the largest displacement since the last
+// bin, canon and nlist (one launch for boxes of up to 12,288 particles, see
+// k_rebuild_small) are launched every step and return at once unless the list
+// is due (host-forced, or the largest displacement since the last
 // build exceeded half the skin -- paper Sec. 5: more movement, more list
 // updates). The decision reads one control word written by the previous
 // step's kernel, so no host synchronisation is needed per step.

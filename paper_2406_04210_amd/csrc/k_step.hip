@@ -272,6 +272,14 @@ __device__ inline void step_ds_body(const StepArgs &a, const BoxC &box, Ctl *ctl
                 }
             }
         } else {
+            // What bounds the kernel here is the gathers: a compute unit's
+            // cache takes one to two lanes of them per clock, hit or not (0.98
+            // random, 1.93 in list order, against 4.2 from LDS), so the 19
+            // million of N = 256,000 take 16 to 32 us by themselves. Fewer
+            // vector instructions change nothing; branchless pairs, whose lanes all
+            // stay active, cost 38 us. (The block's partners copied to LDS
+            // gave 27.8 us, but making the lists of their places took 76 us
+            // per list build.)
             // Eight entries per trip (two 16-byte group loads per lane) keep
             // more of the list stream in flight; groups past a list end read
             // padding or other lists (valid indices) and are skipped. (Masking

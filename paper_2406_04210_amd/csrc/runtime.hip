@@ -57,8 +57,8 @@ struct AdjRecord {
 // particles: 43.4 us with a wait and a pageable copy, 34.0 us with one copy on
 // the stream into pinned memory and one wait). One page serves every context
 // of the process (hipHostMalloc and hipHostFree take about 85 us): allocated
-// with the first context, freed with the last; contexts beyond its slots, or
-// a failed allocation, fall back to pageable copies.
+// when the first context reads its words, freed with the last of them; contexts
+// beyond its slots, or a failed allocation, fall back to pageable copies.
 class PinnedCtl {
 public:
     static constexpr int kSlots = 64;
@@ -121,6 +121,7 @@ struct ljmd_ctx {
     uint64_t gen = 0;
     AdjRecord adj;
     Ctl *pinned = nullptr;  // this context's slot of g_pinned (may be null)
+    bool pinned_asked = false;
     ~ljmd_ctx() {
         g_pinned.release(pinned);
         for (hipEvent_t e : ev_pool) (void)hipEventDestroy(e);
@@ -690,6 +691,10 @@ int run_steps(ljmd_ctx *c, int64_t nsteps, double *obs_dev, const RunOpts &o) {
 
 // Control words after the work enqueued so far (synchronises).
 int read_ctl(ljmd_ctx *c, Ctl *h) {
+    if (!c->pinned_asked) {
+        c->pinned = g_pinned.acquire();
+        c->pinned_asked = true;
+    }
     Ctl *to = c->pinned ? c->pinned : h;
     hipError_t e = hipMemcpyAsync(to, c->st.ctl, sizeof *h, hipMemcpyDeviceToHost, c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "read control words");
@@ -1168,7 +1173,6 @@ int ljmd_create(const ljmd_params *p, void *ws, size_t bytes, void *stream, ljmd
         delete c;
         return rc;
     }
-    c->pinned = g_pinned.acquire();
     *out = c;
     return LJMD_OK;
 }
