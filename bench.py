@@ -35,7 +35,7 @@ HBM_PEAK_GBS = 8000.0
 # 512 MiB copy reads), valid only for the kernel sources they were taken on.
 STEP_KERNEL_SOURCES = ("k_step.hip", "step_common.h", "internal.h")
 STEP_KERNEL_TRAFFIC = {
-    "sources_sha256": "aa39f45e67b6d64d713dfa89f76c56aad8c2859c3c19b0569d4af8c23d7ad9ee",
+    "sources_sha256": "f987689dd5264eecc0d8f829c18b0029e9f29f7464ca65f05bea6ebf2a6c71ef",
     "fetch_bytes": 2.0 * 53431 * 1024,
     "write_bytes": 1.0 * 16128 * 1024,
 }

@@ -422,7 +422,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
 }
 template <int NS, int LANES, bool Q, bool OBS, bool TH, bool PLAIN>
 constexpr void (*step_ds_kernel())(StepArgs) {
-    if constexpr (NS == 2 && !TH)
+    if constexpr (LANES == 2 && Q && TH)
+        return nullptr;  // k_step_ds_small or k_step_ds_fine
+    else if constexpr (NS == 2 && !TH)
         return k_step_ds_mix<LANES, Q, OBS, PLAIN>;
     else
         return k_step_ds<NS, LANES, Q, OBS, TH, PLAIN>;
