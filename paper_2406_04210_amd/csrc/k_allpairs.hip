@@ -16,13 +16,15 @@
 //                   tail of the list path (finalize, thermostat, observable
 //                   terms, integrate) and the deterministic block partials.
 //
-// The j split S spreads a small system over the chip (N = 2,000: 32 tiles x
-// 16 splits = 512 blocks, 2,048 waves); large systems take S = 1.
+// The j split S spreads a system over the chip (N = 2,000: 32 tiles x 16 splits
+// = 512 blocks, 2,048 waves; see allpairs_splits); from 131,072 particles on
+// S = 1.
 #include "step_common.h"
 
 namespace ljmd {
 
 constexpr int kApWaves = 4;            // waves per force block
+constexpr int kApRowsAtOnce = 16;      // split rows per round of loads of the step tail
 constexpr int kApChunk = 1024;         // records staged in LDS at a time
 
 // Partial rows: forces (fx, fy, fz, -) and (e, w) per split and slot.
@@ -179,7 +181,7 @@ template <int PREC, bool TH>
 __global__ __launch_bounds__(kApFinishBlock) void k_ap_finish(StepArgs a, const void *part, int nsplit) {
     using F = typename ApRow<PREC>::F;
     constexpr int BS = kApFinishBlock;
-    constexpr int UR = 16;  // split rows per round of loads
+    constexpr int UR = kApRowsAtOnce;
     Ctl *ctl = a.st.ctl;
     const int64_t i = (int64_t)blockIdx.x * BS + threadIdx.x;
     const size_t stride = (size_t)a.g.max_blocks * BS;
@@ -244,11 +246,22 @@ __global__ __launch_bounds__(kApFinishBlock) void k_ap_finish(StepArgs a, const 
     block_finish<true, BS>(a, ctl, blockIdx.x, pu, pw, pk, ppx, ppy, ppz, dm);
 }
 
-// Splits of the j range: enough blocks for about 2,048 waves, at most one
-// split per tile.
+// Splits of the j range: as many blocks as just fit a whole number of blocks on
+// each of the 256 compute units, since the pass takes as long as the unit with
+// the most; two for each, and up to eight while the step tail can load all of a
+// slot's rows in one round; at most one split per tile. Against the splits that
+// just exceed two blocks on each unit, per step at 1,500 / 3,000 / 4,000 / 5,000
+// / 6,000 / 8,000 particles: FP32 14.5 -> 13.8 / 18.0 -> 16.3 / 23.5 -> 20.4 /
+// 32.8 -> 25.7 / 40.8 -> 31.6 / 59.1 -> 45.2 us, FP64 16.1 -> 14.6 / 26.8 -> 22.5
+// / 38.4 -> 32.4 / 55.6 -> 44.5 / 74.7 -> 57.1 / 115 -> 91; at 12,000 / 32,000
+// FP32 143 -> 102 / 608 -> 545, FP64 284 -> 212 / 1402 -> 1300. FP32 sums get
+// shorter and their error smaller (8,000: 7.6e-7 -> 6.1e-7 of the rms force).
 int allpairs_splits(int64_t n) {
+    constexpr int64_t kUnits = 256;
     const int64_t tiles = (n + kWave - 1) / kWave;
-    int64_t s = (2048 + kApWaves * tiles - 1) / (kApWaves * tiles);
+    int64_t s = 2 * kUnits / tiles;
+    for (int64_t k = 3; k <= 8; ++k)
+        if (k * kUnits / tiles <= kApRowsAtOnce) s = k * kUnits / tiles;
     if (s > tiles) s = tiles;
     return (int)(s < 1 ? 1 : s);
 }

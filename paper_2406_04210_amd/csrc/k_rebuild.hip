@@ -732,8 +732,8 @@ __device__ inline void nlist_cell_as(const State &st, const Geom &g, const BoxC 
         const bool last_part = s0 + kWave >= nst;
         // At least one round for the last part, so that the queues drain.
         for (int cb = 0; cb < ncand || (cb == 0 && last_part); cb += CL * kWave) {
-            // Blocks of 64 candidates this round holds (wave-uniform): the
-            // last round of a cell is usually short.
+            // Blocks of 64 candidates this trip holds (wave-uniform): the
+            // last trip of a cell is usually short.
             const int nbk = min(CL, (ncand - cb + kWave - 1) / kWave);
             T cand[CL];
             bool cv[CL];

@@ -124,3 +124,28 @@ def test_pair_passes_by_lanes(ljmd, n, lanes):
         assert np.abs(a - b).max() <= 1e-10 * max(1.0, np.abs(b).max())
     assert np.abs(fm - fm4).max() <= 1e-10 * fm4.max()
     assert np.abs(xr - xr4).max() <= 1e-10 * w.box[0]
+
+
+@pytest.mark.parametrize("prec", [0, FP32_DS])
+@pytest.mark.parametrize("n", [65, 1537, 2049, 8000, 12289])
+def test_all_pairs_splits(ljmd, n, prec):
+    """All-to-all forces, energy and a step where the number of splits of the
+    partners changes: one, one less or many more than two blocks per compute
+    unit need, ragged last splits (tolerances of test_gpu_allpairs.py). The
+    positions are off the lattice: pairs exactly half a box apart have no
+    nearest image."""
+    w = W.all_pairs_fluid(n=n, seed_index=3)
+    x = (w.x + 0.03 * np.random.default_rng(n).standard_normal(w.x.shape)) % w.box
+    s = ljmd.System(n, w.box, w.params, precision=prec)
+    s.set_state(x, w.v, w.species)
+    f = s.forces().cpu().numpy()
+    o = s.observables()
+    ref, U, Wv, A = reference(x, w.species, w.box, w.params, prec)
+    m = report(f"all pairs n={n} prec={prec}", force_errors(f, ref, A))
+    assert m[bound_key(prec)] <= (1e-12 if prec == 0 else 1e-5), m
+    tol = 1e-12 if prec == 0 else 5e-6
+    assert abs(o["U"] - U) <= tol * abs(U) and abs(o["W"] - Wv) <= tol * abs(Wv)
+    obs = s.run(2).cpu().numpy()
+    v = s.get_state()[1].cpu().numpy()
+    K = 0.5 * (v ** 2).sum()
+    assert abs(obs[-1, 1] - K) <= 2e-6 * K
