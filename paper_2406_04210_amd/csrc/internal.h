@@ -314,8 +314,12 @@ __device__ inline int cell_of_q(uint32_t qx, uint32_t qy, uint32_t qz, const Box
 // list: the kernels return at once, and the first step kernel to see the
 // error records its step (halt = step + 1), from which the host redoes the
 // run after growing the list. The flags are written by earlier kernels of
-// the stream (or by this kernel, for a non-finite position, after which the
-// state is lost anyway), so every block of a launch sees the same value.
+// the stream, but also by blocks of the launch that reads them (list and cell
+// overflows of the list builds, a non-finite position in a step), so two waves
+// of one launch may see different values. A kernel whose waves share LDS after
+// the check reads them once per block, behind a barrier; the step kernels need
+// not (their own launch latches only the non-finite position, after which the
+// state is lost anyway, and what they share are sums, no indices).
 __device__ inline bool halted(const Ctl *ctl) { return ctl->flags != 0u; }
 __device__ inline bool halted_record(Ctl *ctl, int64_t step, bool recorder) {
     if (ctl->flags == 0u) return false;

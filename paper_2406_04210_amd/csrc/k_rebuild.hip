@@ -966,9 +966,17 @@ __global__ __launch_bounds__(kRebuildSmallWaves * kWave) void k_rebuild_small(St
     using CR = CellRec<PREC>;
     using T = typename CR::T;
     constexpr int W = kRebuildSmallWaves, CH = NlistChunk<PREC>::CH;
-    if (blockIdx.x == 0 && threadIdx.x == 0) st.ctl->maxd[(step + 1) & 1] = 0u;
-    if (halted(st.ctl) || !rebuild_due(st.ctl, step, forced, thr2)) return;
-    if (blockIdx.x == 0 && threadIdx.x == 0) st.ctl->rebuilds += 1;
+    // The block leaves or stays as a whole: its waves share LDS below, and the
+    // blocks of this launch themselves latch errors, so that two waves reading
+    // the flags for themselves could see different values.
+    __shared__ int go;
+    if (threadIdx.x == 0) {
+        if (blockIdx.x == 0) st.ctl->maxd[(step + 1) & 1] = 0u;
+        go = !halted(st.ctl) && rebuild_due(st.ctl, step, forced, thr2);
+        if (go && blockIdx.x == 0) st.ctl->rebuilds += 1;
+    }
+    __syncthreads();
+    if (!go) return;
     extern __shared__ uint16_t small_sm[];
     __shared__ int hist[W][32];      // survivors per wave and stencil cell, then positions
     __shared__ int total[3];         // candidates; first home particle among them, home particles
@@ -1110,11 +1118,13 @@ __global__ __launch_bounds__(kRebuildSmallWaves * kWave) void k_rebuild_small(St
         }
         if ((homes >> lane) & 1ull) {
             const int i = CR::index(hrec);
-            uint32_t q[3];
-            rec_q(hrec, box, q);
-            st.nbr_cnt[i] = kreg;
-            st.xref[i] = make_int4((int)q[0], (int)q[1], (int)q[2], CR::species(hrec));
-            if (kreg > g.cap) atomicOr(&st.ctl->flags, kErrList);
+            if ((unsigned)i < (unsigned)g.n) {
+                uint32_t q[3];
+                rec_q(hrec, box, q);
+                st.nbr_cnt[i] = kreg;
+                st.xref[i] = make_int4((int)q[0], (int)q[1], (int)q[2], CR::species(hrec));
+                if (kreg > g.cap) atomicOr(&st.ctl->flags, kErrList);
+            }
         }
     }
 }
