@@ -9,11 +9,10 @@
 // reads every candidate with one contiguous 16-byte (FP32) or 32-byte (FP64)
 // load instead of an index load followed by a dependent gather.
 //
-// bin, canon and nlist (one launch for boxes of up to 12,288 particles, see
-// k_rebuild_small) are launched every step and return at once unless the list
-// is due (host-forced, or the largest displacement since the last
-// build exceeded half the skin -- paper Sec. 5: more movement, more list
-// updates). The decision reads one control word written by the previous
+// bin, canon and nlist (one launch for small boxes, see k_rebuild_small) are
+// launched every step and return at once unless the list is due (host-forced,
+// or the largest displacement since the last build exceeded half the skin --
+// paper Sec. 5: more movement, more list updates). The decision reads one control word written by the previous
 // step's kernel, so no host synchronisation is needed per step.
 #include <algorithm>
 
@@ -945,9 +944,9 @@ __global__ __launch_bounds__(kNlWaves * kWave, (nlist_waves<PREC, NS>())) void k
 // What it replaces is bound by latency at these sizes: three launches a step
 // that mostly return at once, and per rebuild two passes of ~5 us and one wave
 // per cell (64 waves at 2,048 particles: 91 us in FP64). The scan costs
-// n * cells / 64 wave trips. Per step at 2,000 / 12,000 particles: FP32 21.9 /
-// 19.6 -> 13.2 / 15.4 us, FP64 29.0 / 25.5 -> 16.5 / 19.8 us. The limit is the
-// 64 KiB of LDS a block may ask for (five bytes per particle).
+// n * cells / 64 wave trips, and every step launches a block per cell, due or
+// not. Per step at 2,000 / 12,000 particles of a liquid: FP32 21.9 / 19.6 ->
+// 13.2 / 15.4 us, FP64 29.0 / 25.5 -> 16.5 / 19.8 us.
 constexpr int kRebuildSmallN = 12288;
 constexpr int kRebuildSmallWaves = 16;
 
@@ -1384,8 +1383,23 @@ hipError_t launch_nlist(const Launch &L, int64_t step, int forced) {
     return hipGetLastError();
 }
 
+// Which boxes: up to kRebuildSmallN particles (the 64 KiB of LDS a block may ask
+// for, five bytes per particle), and few enough cells that neither the blocks
+// launched on each step nor the scan outweighs the launches saved. Per step, one
+// launch against three (a rebuild every seventh step): FP32 2,000 particles in
+// 343 / 1,728 / 17,576 cells 9.4 / 12.9 / 49.5 against 12.5 / 12.2 / 13.3 us,
+// 6,000 in 216 / 729 / 1,331 cells 12.1 / 12.4 / 14.3 against 17.0 / 13.6 / 12.8,
+// 12,288 in 512 / 729 / 1,331 cells 15.7 / 15.2 / 17.9 against 16.7 / 15.4 /
+// 14.2; FP64 4,000 in 729 cells 12.0 / 13.6, 6,000 in 729 / 1,089 13.6 / 13.3
+// against 14.1 / 12.7, 12,288 in 512 / 729 17.9 / 17.5 against 18.2 / 16.4. In
+// two dimensions a cell has a third of the partners and twice the cells pay in
+// single precision: 5,000 particles in 900 cells 14.6 / 16.7, 8,000 in 1,444
+// 15.8 / 16.8, 10,000 in 1,764 17.1 / 17.0, 12,288 in 2,209 18.4 / 17.1.
 bool rebuild_in_one_launch(const Geom &g, const BoxC &box) {
-    return !g.all_pairs && g.n <= kRebuildSmallN && box.reach == 1;
+    if (g.all_pairs || g.n > kRebuildSmallN || box.reach != 1) return false;
+    const int64_t ncu = g.ncu > 0 ? g.ncu : 256;
+    const int64_t cells = (int64_t)box.ncell * (g.dim == 2 && g.prec != LJMD_FP64 ? 1 : 2);
+    return cells <= 12 * ncu && cells * g.n <= ((int64_t)13 << 20);
 }
 
 template <int PREC, int NS>

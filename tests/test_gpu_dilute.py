@@ -1,0 +1,99 @@
+"""Boxes of many cells and few particles: the forms of the list build on both
+sides of the lines that cells draw, and a box of millions of cells.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2406_04210_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+FP64, FP32_DS = 0, 1
+
+
+@pytest.fixture(scope="module")
+def ljmd():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2406_04210_amd import ljmd as L
+    return L
+
+
+def gas(n, edge, dim, seed):
+    """n particles at a Maxwellian of T = 1 on sites of a square or cubic lattice
+    that fills the box, kept by a seeded permutation and jittered; where the
+    sites are far apart, two particles 1.1 apart at each."""
+    rng = np.random.default_rng(seed)
+    pairs = n % 2 == 0 and edge / np.ceil((n / 2) ** (1.0 / dim)) > 3.5
+    k = n // 2 if pairs else n
+    m = int(np.ceil(k ** (1.0 / dim) - 1e-9))
+    a = edge / m
+    g = np.stack(np.meshgrid(*[np.arange(m)] * dim, indexing="ij"), -1).reshape(-1, dim)
+    room = 0.5 * (a - 3.2) if pairs else min(0.4, max(0.02, 0.4 * (a - 0.95)))
+    c = a * g[np.sort(rng.permutation(len(g))[:k])] + rng.uniform(-room, room, (k, dim))
+    if pairs:
+        d = rng.standard_normal((k, dim))
+        d *= 0.55 / np.linalg.norm(d, axis=1)[:, None]
+        c = np.concatenate([c - d, c + d])
+    x, v = np.zeros((n, 3)), np.zeros((n, 3))
+    x[:, :dim] = c % edge
+    v[:, :dim] = rng.standard_normal((n, dim))
+    return x, v
+
+
+def check_lists(s, x, sp, box, p, prec):
+    cnt, ids = s.neighbors(cap=128)
+    s.sync()
+    cnt, ids = cnt.cpu().numpy(), ids.cpu().numpy()
+    oc, on = oracle.build_lists(x, sp, box, p, mode=0 if prec == FP64 else 1, cap=128)
+    assert np.array_equal(cnt, oc)
+    k = np.arange(128)[None, :] < cnt[:, None]
+    far = np.int64(len(x))
+    assert np.array_equal(np.sort(np.where(k, ids, far), 1), np.sort(np.where(k, on, far), 1))
+
+
+@pytest.mark.parametrize("prec", [FP64, FP32_DS])
+@pytest.mark.parametrize("n,cells,dim", [
+    (500, 11, 3), (500, 12, 3), (6000, 10, 3), (6000, 11, 3), (12288, 8, 3), (12288, 9, 3),
+    (4500, 38, 2), (4500, 39, 2), (8000, 41, 2), (8000, 42, 2), (3000, 30, 3), (12288, 60, 3)])
+def test_lists_by_cells(ljmd, prec, n, cells, dim):
+    edge = 2.8 * 1.001 * cells
+    x, v = gas(n, edge, dim, n + cells)
+    p = W.single_species_params()
+    p.dim = dim
+    box = (edge, edge, edge if dim == 3 else 10.0)
+    sp = np.zeros(n, dtype=np.int32)
+    s = ljmd.System(n, box, p, precision=prec, sort_interval=0)
+    assert ljmd.cell_grid(s.params) == (cells, cells, cells if dim == 3 else 1)
+    s.set_state(x, v, sp)
+    check_lists(s, x, sp, box, p, prec)
+    # Again where the run rebuilt the lists itself.
+    obs = s.run(25).cpu().numpy()
+    last = int(np.nonzero(obs[:, 6])[0][-1]) + 1
+    s.set_state(x, v, sp)
+    s.run(last, observe=False)
+    check_lists(s, s.get_state()[0].cpu().numpy(), sp, box, p, prec)
+
+
+@pytest.mark.parametrize("prec", [FP64, FP32_DS])
+def test_millions_of_cells(ljmd, prec):
+    # 164 cells along each edge: a block of 1,024 threads for each would be more
+    # threads than a launch may have.
+    n, cells = 300, 164
+    edge = 2.8 * 1.001 * cells
+    x, v = gas(n, edge, 3, 7)
+    p = W.single_species_params()
+    s = ljmd.System(n, (edge,) * 3, p, precision=prec, cell_capacity=8)
+    assert np.prod(ljmd.cell_grid(s.params)) * 1024 >= 1 << 32
+    s.set_state(x, v, np.zeros(n, dtype=np.int32))
+    cnt = s.neighbors(cap=16)[0].cpu().numpy()
+    assert np.array_equal(cnt, oracle.build_lists(x, np.zeros(n, dtype=np.int32), (edge,) * 3, p,
+                                                  mode=0 if prec == FP64 else 1, cap=16)[0])
+    assert cnt.min() == 1
+    obs = s.run(20).cpu().numpy()
+    s.sync()
+    assert obs[:, 6].any()
+    r = oracle.run_nve(x, v, np.zeros(n, dtype=np.int32), (edge,) * 3, p, 20)
+    tol = 1e-10 if prec == FP64 else 1e-4  # as test_gpu_parity.py
+    assert np.abs(s.unwrapped_positions().cpu().numpy() - r["x"]).max() <= tol
