@@ -375,6 +375,7 @@ struct NlistChunk {
 constexpr int kNlWaves = 4;
 constexpr int kNlQueueCellsPerCu = 384;  // two species, FP64: queues from this many cells per compute unit on
 constexpr int kNlQueueBlocksPerCu = 5;
+constexpr int kNlStrideBlocksPerCu = 12;  // dilute boxes (see nlist_launch)
 
 __device__ inline int lane_read(int v, int p) { return __builtin_amdgcn_readlane(v, p); }
 __device__ inline int4 lane_read(const int4 &v, int p) {
@@ -886,25 +887,30 @@ __device__ inline void nlist_cell(const State &st, const Geom &g, const BoxC &bo
 // Waves per SIMD the list build's registers are held to. One species: six
 // (80 registers). Two species: five without spills; six spill, and large boxes
 // (the per-XCD queues) run five waves anyway: 1.30 against 1.33 ms per rebuild
-// of the 4M mixture. FP64: four (96-100 registers).
-template <int PREC, int NS>
+// of the 4M mixture. FP64: four (96-100 registers). One species going on from
+// cell to cell (LOOP) spills at six.
+template <int PREC, int NS, bool LOOP>
 constexpr int nlist_waves() {
-    return PREC == LJMD_FP64 ? 4 : (NS == 2 ? 5 : 6);
+    return PREC == LJMD_FP64 ? 4 : (NS == 2 || LOOP ? 5 : 6);
 }
 
-template <int PREC, int NS, bool QC, int LG = -1>
-__global__ __launch_bounds__(kNlWaves * kWave, (nlist_waves<PREC, NS>())) void k_nlist(
-    State st, Geom g, BoxC box, PairC pc, int cur, int64_t step, int forced, float thr2, int halves) {
+// LOOP false: a wave builds one cell, or half of one (halves: its waves 2 c and
+// 2 c + 1 take one group of home particles each). LOOP true: a fixed grid of
+// waves, each going on to a next cell: every stride-th one, or (queued) the
+// next of its XCD's share.
+template <int PREC, int NS, bool QC, int LG, bool LOOP>
+__global__ __launch_bounds__(kNlWaves * kWave, (nlist_waves<PREC, NS, LOOP>())) void k_nlist(
+    State st, Geom g, BoxC box, PairC pc, int cur, int64_t step, int forced, float thr2, int halves, int queued) {
     if (halted(st.ctl) || !rebuild_due(st.ctl, step, forced, thr2)) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) st.ctl->rebuilds += 1;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), W = blockDim.x >> 6;
     __shared__ NlistLds<PREC, QC> sm_all[kNlWaves];
     NlistLds<PREC, QC> &sm = sm_all[wv];
     const auto *rec = records<PREC>(st, cur);
-    if ((PREC != LJMD_FP64 && NS == 1) || (int64_t)box.ncell <= (int64_t)gridDim.x * W) {
-        // A cell, or half of one, per wave: Hilbert-ranked cells, each XCD one
-        // contiguous share of the box.
-        const int gw = xcd_remap(blockIdx.x, gridDim.x) * W + wv;
+    // Hilbert-ranked cells, each XCD one contiguous share of the box (of every
+    // stride).
+    const int gw = xcd_remap(blockIdx.x, gridDim.x) * W + wv;
+    if constexpr (!LOOP) {
         const int c = QC && halves ? gw >> 1 : gw;
         if (c < box.ncell)
             nlist_cell<PREC, NS, QC, LG>(st, g, box, pc, st.rank_of, st.cell_pos, 0, c, st.ctl, rec, sm,
@@ -916,12 +922,14 @@ __global__ __launch_bounds__(kNlWaves * kWave, (nlist_waves<PREC, NS>())) void k
     // share, since cells differ in occupancy. Every wave leaves once its share
     // is used up. (The grid has eight blocks at least.)
     const int q = (int)(blockIdx.x % 8u);
-    const int lo = (int)((int64_t)box.ncell * q / 8), hi = (int)((int64_t)box.ncell * (q + 1) / 8);
+    const int lo = (int)((int64_t)box.ncell * q / 8);
+    const int hi = queued ? (int)((int64_t)box.ncell * (q + 1) / 8) : box.ncell;
     const int lane = threadIdx.x & 63;
-    for (;;) {
-        int c = 0;
-        if (lane == 0) c = lo + (int)atomicAdd(&st.ctl->nlq[q], 1u);
-        c = __builtin_amdgcn_readfirstlane(c);  // wave-uniform from here on
+    for (int c = gw;; c += gridDim.x * W) {
+        if (queued) {
+            if (lane == 0) c = lo + (int)atomicAdd(&st.ctl->nlq[q], 1u);
+            c = __builtin_amdgcn_readfirstlane(c);  // wave-uniform from here on
+        }
         if (c >= hi) break;
         nlist_cell<PREC, NS, QC, LG>(st, g, box, pc, st.rank_of, st.cell_pos, 0, c, st.ctl, rec, sm, -1);
     }
@@ -1356,20 +1364,43 @@ static void nlist_launch(const Launch &L, int64_t step, int forced) {
     // (FP64), 32.9 -> 28.8 (FP64 mixture); at 64,000 (2,900 cells) no
     // difference, at 100,000 30.9 -> 31.4.
     const int halves = L.box->cubic && (int64_t)L.box->ncell <= (int64_t)8 * ncu ? 1 : 0;
-    const unsigned need = blocks_for((int64_t)L.box->ncell * (halves ? 2 : 1), kNlWaves);
-    const bool queued = (PREC == LJMD_FP64 || NS == 2) && (int64_t)L.box->ncell >= (int64_t)kNlQueueCellsPerCu * ncu;
-    const unsigned nb = queued ? std::max(8u, ncu * kNlQueueBlocksPerCu) : need;
+    const int64_t need = ((int64_t)L.box->ncell * (halves ? 2 : 1) + kNlWaves - 1) / kNlWaves;
+    // Dilute boxes, of more cells than two thirds of the particles: most waves
+    // would find an empty cell, and on the steps that return at once their
+    // launch is what there is to pay for. A fixed grid strides over the cells
+    // (always from 2^23 blocks on: a launch may have less than 2^32 threads).
+    // Per step, a wave per cell against it: 20,000 particles in 42,875 / 175,616
+    // / 884,736 cells 19.7 / 31.3 / 81.7 against 18.9 / 21.6 / 34.8 us, 100,000
+    // in 42,875 / 85,184 / 438,976 cells 27.3 / 35.1 / 82.9 against 28.0 / 33.1 /
+    // 48.6, 400,000 in 85,184 / 175,616 / 884,736 59.9 / 79.1 / 214 against 59.7 /
+    // 78.2 / 144 (with 6 / 24 / 48 blocks per compute unit 167 / 137 / 136).
+    const bool dilute = (3 * (int64_t)L.box->ncell > 2 * L.g->n && need > (int64_t)ncu * kNlStrideBlocksPerCu) ||
+                        need > ((int64_t)1 << 23);
+    const bool queued = !dilute && (PREC == LJMD_FP64 || NS == 2) &&
+                        (int64_t)L.box->ncell >= (int64_t)kNlQueueCellsPerCu * ncu;
+    const bool loop = dilute || queued;
+    const dim3 bs(kNlWaves * kWave),
+        nb(queued ? std::max(8u, ncu * kNlQueueBlocksPerCu) : (dilute ? ncu * kNlStrideBlocksPerCu : (unsigned)need));
+#define NLIST_AS(QC, LG, LOOP)                                                                            \
+    hipLaunchKernelGGL((k_nlist<PREC, NS, QC, LG, LOOP>), nb, bs, 0, L.stream, *L.st, *L.g, *L.box, *L.pc, \
+                       L.cur, step, forced, L.dyn->thr2, halves, queued ? 1 : 0)
+#define NLIST(QC, LG)                     \
+    do {                                  \
+        if (loop) NLIST_AS(QC, LG, true); \
+        else NLIST_AS(QC, LG, false);     \
+    } while (0)
     // The common layout of the single-precision force pass (two lanes per
     // particle) has its own instantiation with the entry index folded.
-    if (PREC == LJMD_FP32_DS && L.box->cubic && L.g->lanes == 2)
-        hipLaunchKernelGGL((k_nlist<PREC, NS, PREC == LJMD_FP32_DS, 1>), dim3(nb), dim3(kNlWaves * kWave), 0,
-                           L.stream, *L.st, *L.g, *L.box, *L.pc, L.cur, step, forced, L.dyn->thr2, halves);
-    else if (L.box->cubic)
-        hipLaunchKernelGGL((k_nlist<PREC, NS, true>), dim3(nb), dim3(kNlWaves * kWave), 0, L.stream,
-                           *L.st, *L.g, *L.box, *L.pc, L.cur, step, forced, L.dyn->thr2, halves);
-    else
-        hipLaunchKernelGGL((k_nlist<PREC, NS, false>), dim3(nb), dim3(kNlWaves * kWave), 0, L.stream, *L.st,
-                           *L.g, *L.box, *L.pc, L.cur, step, forced, L.dyn->thr2, halves);
+    if constexpr (PREC == LJMD_FP32_DS) {
+        if (L.box->cubic && L.g->lanes == 2) {
+            NLIST(true, 1);
+            return;
+        }
+    }
+    if (L.box->cubic) NLIST(true, -1);
+    else NLIST(false, -1);
+#undef NLIST
+#undef NLIST_AS
 }
 
 hipError_t launch_nlist(const Launch &L, int64_t step, int forced) {

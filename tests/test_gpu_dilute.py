@@ -97,3 +97,23 @@ def test_millions_of_cells(ljmd, prec):
     r = oracle.run_nve(x, v, np.zeros(n, dtype=np.int32), (edge,) * 3, p, 20)
     tol = 1e-10 if prec == FP64 else 1e-4  # as test_gpu_parity.py
     assert np.abs(s.unwrapped_positions().cpu().numpy() - r["x"]).max() <= tol
+
+
+@pytest.mark.parametrize("prec,two", [(FP64, False), (FP64, True), (FP32_DS, False), (FP32_DS, True)])
+@pytest.mark.parametrize("n,cells,dim", [(20735, 24, 3), (20736, 24, 3), (5000, 23, 3), (19860, 31, 3),
+                                         (15000, 55, 3), (20000, 190, 2)])
+def test_lists_of_many_cells(ljmd, prec, two, n, cells, dim):
+    # A wave per cell (up to 12,288 cells, or at least two particles for three
+    # cells), and a grid that strides over them: on both sides of either line,
+    # and where one wave takes fourteen.
+    edge = 2.8 * 1.001 * cells
+    x, v = gas(n, edge, dim, n + cells)
+    p = W.binary_mixture_params() if two else W.single_species_params()
+    p.rcut[:] = 2.5
+    p.dim = dim
+    box = (edge, edge, edge if dim == 3 else 10.0)
+    sp = (np.random.default_rng(n).uniform(size=n) < 0.2).astype(np.int32) if two else np.zeros(n, dtype=np.int32)
+    s = ljmd.System(n, box, p, precision=prec)
+    assert ljmd.cell_grid(s.params) == (cells, cells, cells if dim == 3 else 1)
+    s.set_state(x, v, sp)
+    check_lists(s, x, sp, box, p, prec)
