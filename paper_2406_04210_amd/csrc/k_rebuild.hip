@@ -1357,13 +1357,21 @@ hipError_t launch_resort(const Launch &L) {
 template <int PREC, int NS>
 static void nlist_launch(const Launch &L, int64_t step, int forced) {
     const unsigned ncu = L.g->ncu > 0 ? (unsigned)L.g->ncu : 256u;
+    // The reduction by bounding boxes in cubic boxes; in FP64, where the exact
+    // test of every candidate decides the same lists, from eight particles a cell
+    // on: below, setting up the boxes costs more than they spare. Per step with
+    // the reduction against without: 100,000 particles at 1.2 / 2.3 / 7.2 / 9.4 /
+    // 14.6 a cell 37.8 / 32.5 / 31.1 / 32.9 / 36.5 against 30.5 / 27.8 / 30.5 /
+    // 33.5 / 38.5 us, 300,000 at 3.5 / 7.0 / 9.2 / 19 64.6 / 61.7 / 68.1 / 86.0
+    // against 56.1 / 58.6 / 63.6 / 94.9.
+    const bool reduce = L.box->cubic && (PREC != LJMD_FP64 || L.g->n >= 8 * (int64_t)L.box->ncell);
     // Few cells (at most eight per compute unit, two waves per SIMD): each
     // cell's two groups of home particles go to a wave of their own, which
     // halves the longest chain of a build for one more candidate search per
     // cell. Per step at 32,000 particles 22.4 -> 21.1 us (FP32), 25.6 -> 24.1
     // (FP64), 32.9 -> 28.8 (FP64 mixture); at 64,000 (2,900 cells) no
     // difference, at 100,000 30.9 -> 31.4.
-    const int halves = L.box->cubic && (int64_t)L.box->ncell <= (int64_t)8 * ncu ? 1 : 0;
+    const int halves = reduce && (int64_t)L.box->ncell <= (int64_t)8 * ncu ? 1 : 0;
     const int64_t need = ((int64_t)L.box->ncell * (halves ? 2 : 1) + kNlWaves - 1) / kNlWaves;
     // Dilute boxes, of more cells than two thirds of the particles: most waves
     // would find an empty cell, and on the steps that return at once their
@@ -1397,7 +1405,7 @@ static void nlist_launch(const Launch &L, int64_t step, int forced) {
             return;
         }
     }
-    if (L.box->cubic) NLIST(true, -1);
+    if (reduce) NLIST(true, -1);
     else NLIST(false, -1);
 #undef NLIST
 #undef NLIST_AS

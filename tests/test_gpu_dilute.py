@@ -117,3 +117,17 @@ def test_lists_of_many_cells(ljmd, prec, two, n, cells, dim):
     assert ljmd.cell_grid(s.params) == (cells, cells, cells if dim == 3 else 1)
     s.set_state(x, v, sp)
     check_lists(s, x, sp, box, p, prec)
+
+
+@pytest.mark.parametrize("n,cells", [(17575, 13), (17576, 13), (117648, 49), (117649, 49)])
+def test_fp64_lists_with_and_without_the_reduction(ljmd, n, cells):
+    # Eight particles a cell are the line below which every candidate is tested
+    # exactly (2,197 cells), and one a cell lies far below it (striding grid).
+    edge = 2.8 * 1.001 * cells
+    x, v = gas(n, edge, 3, n)
+    p = W.single_species_params()
+    box = (edge,) * 3
+    sp = np.zeros(n, dtype=np.int32)
+    s = ljmd.System(n, box, p, precision=FP64)
+    s.set_state(x, v, sp)
+    check_lists(s, x, sp, box, p, FP64)
