@@ -973,13 +973,16 @@ __global__ __launch_bounds__(kRebuildSmallWaves * kWave) void k_rebuild_small(St
     using CR = CellRec<PREC>;
     using T = typename CR::T;
     constexpr int W = kRebuildSmallWaves, CH = NlistChunk<PREC>::CH;
+    if (blockIdx.x == 0 && threadIdx.x == 0) st.ctl->maxd[(step + 1) & 1] = 0u;
+    // Written before this launch: the same for every wave. (Steps without a
+    // rebuild, the most of them, end here and wait for no barrier.)
+    if (!rebuild_due(st.ctl, step, forced, thr2)) return;
     // The block leaves or stays as a whole: its waves share LDS below, and the
     // blocks of this launch themselves latch errors, so that two waves reading
     // the flags for themselves could see different values.
     __shared__ int go;
     if (threadIdx.x == 0) {
-        if (blockIdx.x == 0) st.ctl->maxd[(step + 1) & 1] = 0u;
-        go = !halted(st.ctl) && rebuild_due(st.ctl, step, forced, thr2);
+        go = !halted(st.ctl);
         if (go && blockIdx.x == 0) st.ctl->rebuilds += 1;
     }
     __syncthreads();
