@@ -63,8 +63,9 @@ hipError_t launch_adjoint_drift(const Launch &L, double4 *lx, double4 *lv, void 
                                 int disp);
 
 // Clear the cell counters if the lists were rebuilt for `step` (in a forward
-// run the step kernel does this).
-hipError_t launch_adjoint_cells(const Launch &L, int64_t step, int forced);
+// run the step kernel does this). record: a latched error is recorded under
+// `step`, so that later builds leave the overflowing lists' lengths standing.
+hipError_t launch_adjoint_cells(const Launch &L, int64_t step, int forced, bool record);
 
 hipError_t launch_adjoint_vec(const Launch &L, int op, const double *src_id, double *dst_id, double4 *a,
                               double4 *b, void *gvec, double scale, const double *dscale = nullptr);

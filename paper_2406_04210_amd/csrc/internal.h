@@ -89,7 +89,7 @@ struct Ctl {
     int32_t max_fill;     // longest current list (computed on request)
     int64_t rebuilds;     // list builds since set_state
     unsigned long long fmax[2];  // steepest descent: max |F| (double bits), by iteration parity
-    int64_t halt;         // 1 + step id of the first step kernel that found an error latched (0: none)
+    int64_t halt;         // 1 + step id of the first step or adjoint kernel that found an error latched (0: none)
     uint32_t nlq[8];      // list-build work queues (next cell), one per XCD; reset before each build
     double last[kNP];     // observables of the last flushed step: U, W, K, px, py, pz, rebuilt, step
 };
@@ -311,8 +311,8 @@ __device__ inline int cell_of_q(uint32_t qx, uint32_t qy, uint32_t qz, const Box
 
 // Once an error is latched (list or cell overflow, non-finite position) no
 // kernel changes the state any more, so that no step runs on a truncated
-// list: the kernels return at once, and the first step kernel to see the
-// error records its step (halt = step + 1), from which the host redoes the
+// list: the kernels return at once, and the first step kernel (of a reverse
+// sweep, adjoint kernel) to see the error records its step (halt = step + 1), from which the host redoes the
 // run after growing the list. The flags are written by earlier kernels of
 // the stream, but also by blocks of the launch that reads them (list and cell
 // overflows of the list builds, a non-finite position in a step), so two waves
@@ -325,6 +325,14 @@ __device__ inline bool halted_record(Ctl *ctl, int64_t step, bool recorder) {
     if (ctl->flags == 0u) return false;
     if (recorder && threadIdx.x == 0 && ctl->halt == 0) ctl->halt = step + 1;
     return true;
+}
+
+// Whether a list build leaves its lists alone: an error latched before its
+// launch. A list overflow that no kernel has acted on yet (halt) is its own: it
+// then counts every list to its end, whenever its blocks start, since the host
+// sizes the growth by the longest.
+__device__ inline bool build_stopped(const Ctl *ctl) {
+    return ((ctl->flags & ~(uint32_t)kErrList) != 0u) | (ctl->halt != 0);
 }
 
 // Whether the list is rebuilt before the force evaluation of a step: forced

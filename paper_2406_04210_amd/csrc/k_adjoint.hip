@@ -170,6 +170,7 @@ __global__ __launch_bounds__(BS) void k_adjoint_pairs(AdjArgs a) {
     const int l = lane & (lanes - 1);
     const int64_t i = (chunk << (6 - lg)) + (lane >> lg);
     const bool valid = i < a.g.n;
+    if (a.clear_cells && blockIdx.x == 0) halted_record(st.ctl, a.step, true);
     if (a.clear_cells && rebuild_due(st.ctl, a.step, a.forced, a.thr2)) {
         const int64_t nthr = (int64_t)gridDim.x * blockDim.x;
         for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < a.box.ncell; c += nthr)
@@ -354,7 +355,8 @@ __global__ __launch_bounds__(BS) void k_adjoint_pairs(AdjArgs a) {
 // reverse sweep are followed by no dynamics step kernel, which does this in a
 // forward run.
 __global__ __launch_bounds__(kBlock) void k_adjoint_cells(State st, BoxC box, int64_t step, int forced,
-                                                          float thr2) {
+                                                          float thr2, int record) {
+    if (record && blockIdx.x == 0) halted_record(st.ctl, step, true);
     if (!rebuild_due(st.ctl, step, forced, thr2)) return;
     const int64_t nthr = (int64_t)gridDim.x * blockDim.x;
     for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < box.ncell; c += nthr)
@@ -598,10 +600,10 @@ static AdjArgs pair_args(const Launch &L, const void *gvec, double4 *gx, double 
     return aa;
 }
 
-hipError_t launch_adjoint_cells(const Launch &L, int64_t step, int forced) {
+hipError_t launch_adjoint_cells(const Launch &L, int64_t step, int forced, bool record) {
     const int nbc = (L.box->ncell + kBlock - 1) / kBlock;
     hipLaunchKernelGGL(k_adjoint_cells, dim3(nbc < 1024 ? nbc : 1024), dim3(kBlock), 0, L.stream, *L.st,
-                       *L.box, step, forced, L.dyn->thr2);
+                       *L.box, step, forced, L.dyn->thr2, record ? 1 : 0);
     return hipGetLastError();
 }
 

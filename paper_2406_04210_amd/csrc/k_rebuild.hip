@@ -901,7 +901,7 @@ constexpr int nlist_waves() {
 template <int PREC, int NS, bool QC, int LG, bool LOOP>
 __global__ __launch_bounds__(kNlWaves * kWave, (nlist_waves<PREC, NS, LOOP>())) void k_nlist(
     State st, Geom g, BoxC box, PairC pc, int cur, int64_t step, int forced, float thr2, int halves, int queued) {
-    if (halted(st.ctl) || !rebuild_due(st.ctl, step, forced, thr2)) return;
+    if (build_stopped(st.ctl) || !rebuild_due(st.ctl, step, forced, thr2)) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) st.ctl->rebuilds += 1;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), W = blockDim.x >> 6;
     __shared__ NlistLds<PREC, QC> sm_all[kNlWaves];
@@ -982,7 +982,7 @@ __global__ __launch_bounds__(kRebuildSmallWaves * kWave) void k_rebuild_small(St
     // the flags for themselves could see different values.
     __shared__ int go;
     if (threadIdx.x == 0) {
-        go = !halted(st.ctl);
+        go = !build_stopped(st.ctl);
         if (go && blockIdx.x == 0) st.ctl->rebuilds += 1;
     }
     __syncthreads();

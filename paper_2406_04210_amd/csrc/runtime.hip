@@ -755,7 +755,8 @@ int check_overflow(ljmd_ctx *c, Ctl *h, bool *redo) {
     hipError_t e = launch_max_fill(launcher(c));
     if (e != hipSuccess) return hip_fail(c, e, "max_fill");
     if ((r = read_ctl(c, h))) return r;
-    if ((r = grow_lists(c, h->max_fill))) return r;
+    // Never less than one more than the room that did not do.
+    if ((r = grow_lists(c, std::max(h->max_fill, c->g.cap + 1)))) return r;
     *redo = true;
     return LJMD_OK;
 }
@@ -842,7 +843,7 @@ int ckpt_copy(ljmd_ctx *c, uint8_t *dst, bool save) {
 int rebuild_at_rest(ljmd_ctx *c, int64_t step) {
     int r = rebuild_sequence(c, step, 1, false);
     if (r) return r;
-    hipError_t e = launch_adjoint_cells(launcher(c), step, 1);
+    hipError_t e = launch_adjoint_cells(launcher(c), step, 1, false);
     return e == hipSuccess ? LJMD_OK : hip_fail(c, e, "clear cells");
 }
 
@@ -1624,7 +1625,7 @@ int ljmd_vv_backward(ljmd_ctx *c, const double *lam_x, const double *lam_v, cons
             L = launcher(c);
             set_rec_ptr(c, c->cur, seg_frames + (size_t)fl * P.frame_stride);
             if ((r = rebuild_sequence(c, t - 1, 1, false))) return r;
-            if ((e = launch_adjoint_cells(L, t - 1, 1)) != hipSuccess) return hip_fail(c, e, "clear cells");
+            if ((e = launch_adjoint_cells(L, t - 1, 1, true)) != hipSuccess) return hip_fail(c, e, "clear cells");
         }
         for (int32_t j = top; j >= 0; --j, ++t) {
             const int64_t s = (int64_t)s0 + j;

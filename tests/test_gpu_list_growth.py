@@ -68,3 +68,48 @@ def test_droplet_overflow_is_recovered(ljmd, box, prec):
     assert np.isfinite(out[0][1]).all()
     for a, b in zip(*out):
         assert np.array_equal(a, b)
+
+
+def clusters(edge, spacings, outside, seed):
+    """Cubic pieces of simple cubic lattices, one per spacing, at places of a
+    3 x 3 x 3 grid, in a lattice of spacing `outside`."""
+    rng = np.random.default_rng(seed)
+    third = edge / 3.0
+    places = np.stack(np.meshgrid(*[np.arange(3)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    side = 0.6 * third
+    m = int(edge / outside)
+    far = (np.stack(np.meshgrid(*[np.arange(m)] * 3, indexing="ij"), -1).reshape(-1, 3) + 0.5) * (edge / m)
+    x = []
+    for place, a in zip(places[rng.permutation(27)[: len(spacings)]], spacings):
+        c = third * (place + 0.5)
+        k = int(side / a)
+        x.append(c + a * (np.stack(np.meshgrid(*[np.arange(k)] * 3, indexing="ij"), -1).reshape(-1, 3) - 0.5 * (k - 1)))
+        far = far[np.abs(far - c).max(axis=1) > 0.5 * side + outside]
+    x = np.concatenate(x + [far])
+    return x + 0.02 * rng.standard_normal(x.shape)
+
+
+@pytest.mark.parametrize("prec", [FP64, FP32_DS])
+@pytest.mark.parametrize("edge,outside", [(45.0, 3.0), (118.0, 1.7), (118.0, 4.0)])
+def test_growth_knows_the_longest_list(ljmd, edge, outside, prec):
+    # Clusters of several densities: whichever list overflows first, the lists
+    # grow once, by the longest of them all.
+    x = clusters(edge, [1.3, 1.2, 1.1, 1.05, 1.0, 0.97, 0.95, 0.92], outside, 3)
+    n, v, sp = len(x), np.zeros_like(x), np.zeros(len(x), dtype=np.int32)
+    p = W.single_species_params()
+    cap, room = 32, 512
+    for seed in range(3):
+        order = np.random.default_rng(seed).permutation(n)
+        ref = ljmd.System(n, (edge,) * 3, p, precision=prec, nbr_capacity=256, cell_capacity=128)
+        ref.set_state(x[order], v, sp)
+        longest = ref.observables()["max_fill"]
+        s = ljmd.System(n, (edge,) * 3, p, precision=prec, nbr_capacity=cap, nbr_capacity_max=room,
+                        cell_capacity=128)
+        s.set_state(x[order], v, sp)
+        o = s.observables()
+        print(f"clusters n={n} cells={ljmd.cell_grid(s.params)} prec={prec} longest={longest} "
+              f"capacity={o['nbr_capacity']} builds={o['rebuilds']}", flush=True)
+        assert o["rebuilds"] == 2
+        assert 64 < longest <= 256
+        assert o["nbr_capacity"] == -(-max(longest + 16, int(np.ceil(1.25 * longest))) // 16) * 16
+        assert np.array_equal(s.forces().cpu().numpy(), ref.forces().cpu().numpy())
