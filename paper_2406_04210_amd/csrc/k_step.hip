@@ -422,9 +422,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
 }
 template <int NS, int LANES, bool Q, bool OBS, bool TH, bool PLAIN>
 constexpr void (*step_ds_kernel())(StepArgs) {
-    if constexpr (LANES == 2 && Q && TH)
-        return nullptr;  // k_step_ds_small or k_step_ds_fine
-    else if constexpr (NS == 2 && !TH)
+    if constexpr (NS == 2 && !TH)
         return k_step_ds_mix<LANES, Q, OBS, PLAIN>;
     else
         return k_step_ds<NS, LANES, Q, OBS, TH, PLAIN>;
@@ -729,13 +727,31 @@ static StepArgs make_args(const Launch &L, int64_t step, int forced, int mode, i
 // the first round even it out.
 // The thermostat's kernel holds 84 registers, more than two blocks of 1024
 // leave room for: it always takes quarters (100,000 particles 21.0 / 20.6,
-// 256,000 37.2 / 35.1, 1,000,000 158.8 / 137.8).
-static bool fine_blocks(const Geom &g, bool th) {
-    if (th) return true;
+// 256,000 37.2 / 35.1, 1,000,000 158.8 / 137.8; see launch_step).
+static bool fine_blocks(const Geom &g) {
     const int64_t ncu = g.ncu > 0 ? g.ncu : 256;
     const int64_t whole = (g.n + kBlock / 2 - 1) / (kBlock / 2), quarters = (g.n + kBlockSmall / 2 - 1) / (kBlockSmall / 2);
     const int64_t load = (whole + ncu - 1) / ncu, load4 = (quarters + ncu - 1) / ncu;
     return load <= 4 && 11 * load4 < 40 * load;
+}
+
+// The kernels in blocks of 1024 threads, and every other layout than two lanes
+// in a cubic box. The thermostat has no such kernel for that layout.
+template <int NS, int LN, bool TH, bool PL>
+static hipError_t step_ds_launch(const Launch &L, dim3 grid, dim3 block, const StepArgs &a, bool quanta, bool obs) {
+    if (!quanta) {
+        launch_k(L, step_ds_kernel<NS, LN, false, true, TH, PL>(), grid, block, a);
+        return hipGetLastError();
+    }
+    if constexpr (LN == 2 && TH) {
+        return hipErrorInvalidDeviceFunction;
+    } else {
+        if (obs)
+            launch_k(L, step_ds_kernel<NS, LN, true, true, TH, PL>(), grid, block, a);
+        else
+            launch_k(L, step_ds_kernel<NS, LN, true, false, TH, PL>(), grid, block, a);
+        return hipGetLastError();
+    }
 }
 
 hipError_t launch_step(const Launch &L, int64_t step, int forced, int mode, int slot) {
@@ -756,7 +772,7 @@ hipError_t launch_step(const Launch &L, int64_t step, int forced, int mode, int 
     // this one; at 100,000 18.6 against 19.4 us, at 256,000 30.1 against 32.1.
     const bool few_waves = L.g->n <= (int64_t)256 * (L.g->ncu > 0 ? L.g->ncu : 256);
     const bool small = quanta && L.g->lanes == 2 && few_waves;
-    if (small || (quanta && L.g->lanes == 2 && fine_blocks(*L.g, th))) {
+    if (small || (quanta && L.g->lanes == 2 && (th || fine_blocks(*L.g)))) {
         const dim3 gs((unsigned)L.g->max_blocks), bs(kBlockSmall);  // every row of partials is written
 #define STEP_256(K, NS, OB)                                                          \
     do {                                                                             \
@@ -792,23 +808,13 @@ hipError_t launch_step(const Launch &L, int64_t step, int forced, int mode, int 
         else launch_k(L, k_step_fp64_small<1, false>, grid, block, a);
         return hipGetLastError();
     }
-#define STEP_DS(NS, LN, TH, PL)                                                                         \
-    do {                                                                                                \
-        if (quanta && obs)                                                                              \
-            launch_k(L, step_ds_kernel<NS, LN, true, true, TH, PL>(), grid, block, a);                   \
-        else if (quanta)                                                                                \
-            launch_k(L, step_ds_kernel<NS, LN, true, false, TH, PL>(), grid, block, a);                  \
-        else                                                                                            \
-            launch_k(L, step_ds_kernel<NS, LN, false, true, TH, PL>(), grid, block, a);                  \
-    } while (0)
-#define STEP_TH(NS, LN, TH)                                                              \
-    do {                                                                                 \
-        if (ds && plain)                                                                 \
-            STEP_DS(NS, LN, TH, true);                                                   \
-        else if (ds)                                                                     \
-            STEP_DS(NS, LN, TH, false);                                                  \
-        else                                                                             \
-            launch_k(L, k_step_fp64<NS, LN, TH>, grid, block, a);                     \
+#define STEP_TH(NS, LN, TH)                                                             \
+    do {                                                                                \
+        if (ds && plain)                                                                \
+            return step_ds_launch<NS, LN, TH, true>(L, grid, block, a, quanta, obs);    \
+        if (ds)                                                                         \
+            return step_ds_launch<NS, LN, TH, false>(L, grid, block, a, quanta, obs);   \
+        launch_k(L, k_step_fp64<NS, LN, TH>, grid, block, a);                           \
     } while (0)
 #define STEP(NS, LN)              \
     do {                          \
@@ -833,7 +839,6 @@ hipError_t launch_step(const Launch &L, int64_t step, int forced, int mode, int 
 #undef BY_LANES
 #undef STEP
 #undef STEP_TH
-#undef STEP_DS
     return hipGetLastError();
 }
 
