@@ -56,15 +56,17 @@ struct AdjRecord {
 // memory is staged by the runtime and waited for twice (run(1) of 500
 // particles: 43.4 us with a wait and a pageable copy, 34.0 us with one copy on
 // the stream into pinned memory and one wait). One page serves every context
-// of the process (hipHostMalloc and hipHostFree take about 85 us): allocated
-// when the first context reads its words, freed with the last of them; contexts
-// beyond its slots, or a failed allocation, fall back to pageable copies.
+// of the process: allocated when the first context reads its words, and kept
+// until the process ends (with hipHostMalloc and hipHostFree for each of them, a
+// program that creates, runs and drops one system after the other pays 39 us a
+// time, and the free waits for the device). Contexts beyond its slots, or a
+// failed allocation, fall back to pageable copies.
 class PinnedCtl {
 public:
     static constexpr int kSlots = 64;
     Ctl *acquire() {
         std::lock_guard<std::mutex> lock(mu_);
-        if (used_ == 0 && hipHostMalloc((void **)&page_, sizeof(Ctl) * kSlots, hipHostMallocPortable) != hipSuccess) {
+        if (!page_ && hipHostMalloc((void **)&page_, sizeof(Ctl) * kSlots, hipHostMallocPortable) != hipSuccess) {
             (void)hipGetLastError();
             page_ = nullptr;
         }
@@ -77,10 +79,6 @@ public:
         if (!slot) return;
         std::lock_guard<std::mutex> lock(mu_);
         used_ &= ~(1ull << (slot - page_));
-        if (used_ == 0) {
-            (void)hipHostFree(page_);
-            page_ = nullptr;
-        }
     }
 
 private:
