@@ -52,7 +52,7 @@ extern "C" {
 enum ljmd_status {
     LJMD_OK = 0,
     LJMD_EINVAL = -1,  /* bad argument or parameter */
-    LJMD_ENOMEM = -2,  /* workspace smaller than ljmd_workspace_size() */
+    LJMD_ENOMEM = -2,  /* workspace smaller than what ljmd_workspace_size() documents */
     LJMD_EHIP = -3,    /* a HIP runtime call failed */
     LJMD_EBOX = -4,    /* box edge < 2 * largest list radius (minimum image breaks) */
     LJMD_ENLIST = -5,  /* a neighbour list exceeded nbr_capacity */
@@ -154,7 +154,10 @@ int ljmd_check_params(const ljmd_params *p);
  * cubic box). ljmd_run, ljmd_set_state, ljmd_get_*, ljmd_observables and
  * the thermostat work as for the truncated potential; the list-based calls
  * (ljmd_neighbors, ljmd_minimize_sd, the gradients and rollouts, the tuner
- * and batches) return LJMD_EINVAL. */
+ * and batches) return LJMD_EINVAL. The size is that of the fastest split of
+ * the pairs; ljmd_create also takes less, down to the rows of ceil(512 /
+ * ceil(n / 64)) splits (at most one per 64 particles), and then splits less:
+ * sums are formed in another order, with the same accuracy. */
 size_t ljmd_workspace_size(const ljmd_params *p);
 
 /* Cell grid the binning uses for these parameters: ncell[0..2] cells per
@@ -467,7 +470,8 @@ const char *ljmd_batch_last_error(const ljmd_batch *b);
  * n*3 float64, any image), species (device, n int32) -> f (device, n*3
  * float64, same order) and uw (device, 2 float64: U = sum phi_s, W = sum
  * r_ij.f_ij over pairs i < j). ws (device, >= ljmd_brute_workspace_size(p)
- * bytes, 256-byte aligned) is scratch, the caller's. Asynchronous on
+ * bytes, 256-byte aligned; less as for the all-pairs interaction in
+ * ljmd_workspace_size) is scratch, the caller's. Asynchronous on
  * hip_stream. Errors: LJMD_EINVAL / LJMD_EBOX (parameters), LJMD_ENOMEM
  * (workspace too small), LJMD_EHIP; text in ljmd_last_error(NULL). */
 size_t ljmd_brute_workspace_size(const ljmd_params *p);

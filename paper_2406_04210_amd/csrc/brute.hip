@@ -78,14 +78,14 @@ int ljmd_brute_forces(const ljmd_params *p, const double *x, const int32_t *spec
     if (r != LJMD_OK) return r;
     if (!x || !species || !f || !uw || !ws) return brute_fail(LJMD_EINVAL, "brute_forces: NULL argument");
     if (((uintptr_t)ws & 255) != 0) return brute_fail(LJMD_EINVAL, "brute_forces: workspace must be 256-byte aligned");
-    if (bytes < brute_scratch_bytes(p->n, p->precision))
+    if (bytes < brute_scratch_least(p->n, p->precision))
         return brute_fail(LJMD_ENOMEM, "brute_forces: workspace smaller than ljmd_brute_workspace_size");
     BoxC box;
     PairC pc;
     box_pair_constants(*p, box, pc);
     const int dim = p->dim == 2 ? 2 : 3;
     const hipError_t e = launch_brute(box, pc, p->precision, p->nspecies, dim, cut_of(p) ? 1 : 0, p->n, x, species,
-                                      f, uw, (uint8_t *)ws, (hipStream_t)stream);
+                                      f, uw, (uint8_t *)ws, bytes, (hipStream_t)stream);
     if (e != hipSuccess) return brute_fail(LJMD_EHIP, hipGetErrorString(e));
     return LJMD_OK;
 }
@@ -97,7 +97,7 @@ int ljmd_brute_forces_noalloc(const ljmd_params *p, const double *x, const int32
     int r = brute_check(p);
     if (r != LJMD_OK) return r;
     if (!x || !species || !f || !uw) return brute_fail(LJMD_EINVAL, "brute_forces_noalloc: NULL argument");
-    const size_t need = brute_scratch_bytes(p->n, p->precision);
+    const size_t need = brute_scratch_least(p->n, p->precision);
     if (need > kStaticScratchBytes) {
         char msg[160];
         std::snprintf(msg, sizeof msg,
@@ -113,7 +113,7 @@ int ljmd_brute_forces_noalloc(const ljmd_params *p, const double *x, const int32
     box_pair_constants(*p, box, pc);
     const int dim = p->dim == 2 ? 2 : 3;
     const hipError_t e = launch_brute(box, pc, p->precision, p->nspecies, dim, cut_of(p) ? 1 : 0, p->n, x, species,
-                                      f, uw, ptr, (hipStream_t)stream);
+                                      f, uw, ptr, kStaticScratchBytes, (hipStream_t)stream);
     if (e != hipSuccess) return brute_fail(LJMD_EHIP, hipGetErrorString(e));
     return LJMD_OK;
 }

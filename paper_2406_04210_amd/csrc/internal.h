@@ -150,6 +150,7 @@ struct Geom {
     int32_t ncu;          // compute units of the device (grid of the per-step rebuild kernels)
     int32_t all_pairs;    // 1: untruncated all-pairs interaction (no lists, no cells)
     int32_t dim;          // 2 (motion in the x-y plane, z and v_z held at 0) or 3
+    int32_t nsplit;       // all pairs: splits of the j range (what the workspace holds rows for)
 };
 
 // ------------------------------------------------------------------------
@@ -396,17 +397,21 @@ hipError_t launch_neighbors(const Launch &L, int32_t *cnt, int32_t *ids, int32_t
 hipError_t launch_max_fill(const Launch &L);
 hipError_t launch_sd(const Launch &L, int64_t step, int forced, int iter, double delta,
                      double clamp, double *fmax_out);
-// All-pairs mode: splits of the j range, bytes of the partial rows (held in
-// the list area), and the two launches of one step.
+// All-pairs mode: splits of the j range (and the fewest a workspace has to
+// hold rows for), bytes of the partial rows (held in the list area), and the
+// two launches of one step.
 int allpairs_splits(int64_t n);
-size_t allpairs_part_bytes(int64_t n, int prec);
+int allpairs_splits_least(int64_t n);
+size_t allpairs_part_bytes(int64_t n, int prec, int nsplit);
 hipError_t launch_allpairs_step(const Launch &L, int64_t step, int mode, int slot);
 // One-shot brute-force forces of a configuration given by id: scratch of
-// brute_scratch_bytes(n, prec) bytes (256-byte aligned); cut: truncate and
-// shift at r_c (else every pair interacts). f (n*3) and uw (U, W) are FP64.
+// brute_scratch_bytes(n, prec) bytes (256-byte aligned), or less, down to
+// brute_scratch_least, for fewer splits; cut: truncate and shift at r_c (else
+// every pair interacts). f (n*3) and uw (U, W) are FP64.
 size_t brute_scratch_bytes(int64_t n, int prec);
+size_t brute_scratch_least(int64_t n, int prec);
 hipError_t launch_brute(const BoxC &box, const PairC &pc, int prec, int nspecies, int dim, int cut, int64_t n,
-                        const double *x, const int32_t *sp, double *f, double *uw, uint8_t *scratch,
+                        const double *x, const int32_t *sp, double *f, double *uw, uint8_t *scratch, size_t bytes,
                         hipStream_t stream);
 // Box and pair constants of a parameter set (cell grid 1x1x1), and the
 // parameter check of ljmd_check_params with its reason.

@@ -19,6 +19,8 @@
 // The j split S spreads a system over the chip (N = 2,000: 32 tiles x 16 splits
 // = 512 blocks, 2,048 waves; see allpairs_splits); from 131,072 particles on
 // S = 1.
+#include <algorithm>
+
 #include "step_common.h"
 
 namespace ljmd {
@@ -266,13 +268,22 @@ int allpairs_splits(int64_t n) {
     return (int)(s < 1 ? 1 : s);
 }
 
-// Bytes of the partial rows for n particles: S rows of (forces, e and w)
+// The fewest splits that a workspace has to hold rows for: what just exceeds two
+// blocks per unit (the size that sufficed before the splits filled the units
+// evenly). Between the two the workspace decides.
+int allpairs_splits_least(int64_t n) {
+    const int64_t tiles = (n + kWave - 1) / kWave;
+    const int64_t s = (2 * 256 + tiles - 1) / tiles;
+    return std::min((int)(s < tiles ? s : tiles), allpairs_splits(n));
+}
+
+// Bytes of the partial rows for n particles: nsplit rows of (forces, e and w)
 // per finish-kernel slot.
-size_t allpairs_part_bytes(int64_t n, int prec) {
+size_t allpairs_part_bytes(int64_t n, int prec, int nsplit) {
     const int bs = kApFinishBlock;
     const size_t slots = (size_t)((n + bs - 1) / bs) * bs;
     const size_t row = (prec == LJMD_FP64 ? sizeof(double4) : sizeof(float4)) + sizeof(double2);
-    return (size_t)allpairs_splits(n) * slots * row;
+    return (size_t)nsplit * slots * row;
 }
 
 hipError_t launch_allpairs_step(const Launch &L, int64_t step, int mode, int slot) {
@@ -288,7 +299,7 @@ hipError_t launch_allpairs_step(const Launch &L, int64_t step, int mode, int slo
     a.slot = slot;
     a.step = step;
     void *part = L.st->nbr;  // the list area holds the partial rows in this mode
-    const int S = allpairs_splits(L.g->n);
+    const int S = L.g->nsplit;
     const int bs = kApFinishBlock;
     ApForce af;
     af.rec = L.g->prec == LJMD_FP64 ? (const void *)L.st->rec64[L.cur] : (const void *)L.st->recq[L.cur];
@@ -438,12 +449,12 @@ struct BruteScratch {
     int nsplit, nb;
 };
 
-static BruteScratch brute_layout(int64_t n, int prec) {
+static BruteScratch brute_layout(int64_t n, int prec, int nsplit) {
     auto al = [](size_t b) { return (b + 255) & ~(size_t)255; };
     BruteScratch b;
     const int64_t npad = (n + kBlock - 1) / kBlock * kBlock;
     b.stride = (size_t)npad;
-    b.nsplit = allpairs_splits(n);
+    b.nsplit = nsplit;
     b.nb = (int)(npad / kBlock);
     const size_t rec = prec == LJMD_FP64 ? sizeof(double4) : sizeof(int4);
     const size_t row = (prec == LJMD_FP64 ? sizeof(double4) : sizeof(float4)) + sizeof(double2);
@@ -453,12 +464,16 @@ static BruteScratch brute_layout(int64_t n, int prec) {
     return b;
 }
 
-size_t brute_scratch_bytes(int64_t n, int prec) { return brute_layout(n, prec).total; }
+size_t brute_scratch_bytes(int64_t n, int prec) { return brute_layout(n, prec, allpairs_splits(n)).total; }
+size_t brute_scratch_least(int64_t n, int prec) { return brute_layout(n, prec, allpairs_splits_least(n)).total; }
 
 hipError_t launch_brute(const BoxC &box, const PairC &pc, int prec, int nspecies, int dim, int cut, int64_t n,
-                        const double *x, const int32_t *sp, double *f, double *uw, uint8_t *scratch,
+                        const double *x, const int32_t *sp, double *f, double *uw, uint8_t *scratch, size_t bytes,
                         hipStream_t stream) {
-    const BruteScratch bl = brute_layout(n, prec);
+    // As many splits as the scratch holds rows for.
+    BruteScratch bl = brute_layout(n, prec, allpairs_splits(n));
+    while (bl.total > bytes && bl.nsplit > 1) bl = brute_layout(n, prec, bl.nsplit - 1);
+    if (bl.total > bytes) return hipErrorInvalidValue;
     ApForce af;
     af.rec = scratch;
     af.part = scratch + bl.off_rows;

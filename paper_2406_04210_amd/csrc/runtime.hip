@@ -247,6 +247,7 @@ struct Plan {
     int nc[3];
     int ncell;
     int max_blocks;       // rows of partials per step
+    int nsplit;           // all pairs: splits of the j range
     // byte offsets
     size_t off_rec[2], off_vel, off_frc, off_dsw[3], off_img, off_id,
         off_xref, off_nbr, off_cnt, off_ccount, off_cmem, off_cstart, off_rank, off_lin, off_scratch,
@@ -263,7 +264,9 @@ int32_t round_up(int32_t v, int32_t m) { return (v + m - 1) / m * m; }
 
 void lay_out(Plan &pl, int prec, int nctl);
 
-Plan make_plan(const ljmd_params *p) {
+// Plan of a parameter set for a workspace of `bytes`: the full one, or, if that
+// needs more, the largest that fits (the smallest there is if none does).
+Plan make_plan(const ljmd_params *p, size_t bytes = SIZE_MAX) {
     Plan pl{};
     pl.npad = (p->n + 63) / 64 * 64;
     grid_dims(p, pl.nc);
@@ -273,13 +276,16 @@ Plan make_plan(const ljmd_params *p) {
         // force rows of the j splits, one particle per lane of the step tail.
         pl.lanes = 1;
         pl.cell_cap = 8;
-        const size_t pb = allpairs_part_bytes(p->n, p->precision);
         pl.cap = 16;
-        pl.cap_reserve = std::max<int32_t>(
-            16, round_up((int32_t)((pb + sizeof(int32_t) * pl.npad - 1) / (sizeof(int32_t) * pl.npad)), 16));
         pl.max_blocks = (int)((p->n + kApFinishBlock - 1) / kApFinishBlock);
-        lay_out(pl, p->precision, 1);
-        return pl;
+        const int least = allpairs_splits_least(p->n);
+        for (pl.nsplit = allpairs_splits(p->n);; --pl.nsplit) {
+            const size_t pb = allpairs_part_bytes(p->n, p->precision, pl.nsplit);
+            pl.cap_reserve = std::max<int32_t>(
+                16, round_up((int32_t)((pb + sizeof(int32_t) * pl.npad - 1) / (sizeof(int32_t) * pl.npad)), 16));
+            lay_out(pl, p->precision, 1);
+            if (pl.total <= bytes || pl.nsplit <= least) return pl;
+        }
     }
     const double vol = p->box[0] * p->box[1] * p->box[2];
     const double rho = (double)p->n / vol;
@@ -1116,7 +1122,7 @@ int ljmd_create(const ljmd_params *p, void *ws, size_t bytes, void *stream, ljmd
     if (r != LJMD_OK) return fail(nullptr, r, "%s", why.c_str());
     if (!ws) return fail(nullptr, LJMD_EINVAL, "workspace is NULL");
     if (((uintptr_t)ws & 255) != 0) return fail(nullptr, LJMD_EINVAL, "workspace must be 256-byte aligned");
-    Plan pl = make_plan(p);
+    Plan pl = make_plan(p, bytes);
     if (bytes < pl.total)
         return fail(nullptr, LJMD_ENOMEM, "workspace has %zu bytes, needs %zu", bytes, pl.total);
     ljmd_ctx *c = new (std::nothrow) ljmd_ctx();
@@ -1134,6 +1140,7 @@ int ljmd_create(const ljmd_params *p, void *ws, size_t bytes, void *stream, ljmd
     g.prec = p->precision;
     g.max_blocks = pl.max_blocks;
     g.all_pairs = all_pairs(p) ? 1 : 0;
+    g.nsplit = pl.nsplit;
     g.dim = dim_of(p);
     g.ncu = 256;
     if (c->device >= 0) {

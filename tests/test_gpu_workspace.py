@@ -1,0 +1,74 @@
+"""Workspaces below the size that ljmd_workspace_size gives, down to what
+ljmd.h documents: taken, with results of the same accuracy; less is refused.
+The byte counts are literals, as in a program that keeps its own.
+"""
+import numpy as np
+import pytest
+
+from force_metrics import bound_key, force_errors, reference, report
+from paper_2406_04210_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+FP64, FP32_DS, FP32 = 0, 1, 2
+
+
+@pytest.fixture(scope="module")
+def ljmd():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2406_04210_amd import ljmd as L
+    return L
+
+
+def all_pairs(n):
+    w = W.all_pairs_fluid(n=n, seed_index=3)
+    return w, (w.x + 0.03 * np.random.default_rng(n).standard_normal(w.x.shape)) % w.box
+
+
+@pytest.mark.parametrize("prec,n,least", [(FP64, 4000, 3084288), (FP64, 12000, 6116096), (FP32_DS, 4000, 2439168),
+                                          (FP32_DS, 8000, 3811840), (FP32, 8000, 3811840)])
+def test_all_pairs_in_less(ljmd, monkeypatch, prec, n, least):
+    w, x = all_pairs(n)
+    # Tolerances of test_gpu_allpairs.py.
+    tol_f, tol = (1e-12, 1e-12) if prec == FP64 else (1e-5, 5e-6)
+    ref, U, Wv, A = reference(x, w.species, w.box, w.params, prec) if prec != FP32 else (None,) * 4
+    full = ljmd.workspace_size(ljmd.make_params(n, w.box, w.params, prec))
+    obs = []
+    for size in (full, (least + full) // 2, least):
+        print(f"all pairs prec={prec} n={n} workspace {size} of {full}", flush=True)
+        monkeypatch.setattr(ljmd, "workspace_size", lambda p: size)
+        s = ljmd.System(n, w.box, w.params, precision=prec)
+        s.set_state(x, w.v, w.species)
+        if ref is not None:
+            m = report(f"all pairs n={n} prec={prec} bytes={size}", force_errors(s.forces().cpu().numpy(), ref, A))
+            assert m[bound_key(prec)] <= tol_f, m
+            o = s.observables()
+            assert abs(o["U"] - U) <= tol * abs(U) and abs(o["W"] - Wv) <= tol * abs(Wv)
+        obs.append(s.run(2).cpu().numpy()[:, :3])
+    assert least < full
+    for o in obs[1:]:
+        assert np.abs(o - obs[0]).max() <= (1e-11 if prec == FP64 else 1e-5) * np.abs(obs[0]).max()
+    monkeypatch.setattr(ljmd, "workspace_size", lambda p: least - 256)
+    with pytest.raises(ljmd.LJMDError) as err:
+        ljmd.System(n, w.box, w.params, precision=prec)
+    assert err.value.code == -2                       # LJMD_ENOMEM
+
+
+@pytest.mark.parametrize("prec,n,least", [(FP64, 4000, 1900800), (FP32_DS, 8000, 1442048)])
+def test_brute_forces_in_less(ljmd, monkeypatch, prec, n, least):
+    w, x = all_pairs(n)
+    ref, U, Wv, A = reference(x, w.species, w.box, w.params, prec)
+    tol_f, tol = (1e-12, 1e-12) if prec == FP64 else (1e-5, 5e-6)
+    for size in (least, least + 400000):
+        print(f"brute prec={prec} n={n} workspace {size}", flush=True)
+        monkeypatch.setattr(ljmd.lib, "ljmd_brute_workspace_size", lambda p: size)
+        f, uw = ljmd.brute_forces(n, w.box, w.params, x, w.species, precision=prec)
+        m = report(f"brute n={n} prec={prec} bytes={size}", force_errors(f.cpu().numpy(), ref, A))
+        assert m[bound_key(prec)] <= tol_f, m
+        uw = uw.cpu().numpy()
+        assert abs(uw[0] - U) <= tol * abs(U) and abs(uw[1] - Wv) <= tol * abs(Wv)
+    monkeypatch.setattr(ljmd.lib, "ljmd_brute_workspace_size", lambda p: least - 256)
+    with pytest.raises(ljmd.LJMDError) as err:
+        ljmd.brute_forces(n, w.box, w.params, x, w.species, precision=prec)
+    assert err.value.code == -2
