@@ -17,8 +17,8 @@
 //                   terms, integrate) and the deterministic block partials.
 //
 // The j split S spreads a system over the chip (N = 2,000: 32 tiles x 16 splits
-// = 512 blocks, 2,048 waves; see allpairs_splits); from 131,072 particles on
-// S = 1.
+// = 512 blocks, 2,048 waves; see allpairs_splits); above 65,536 particles (1,024
+// tiles) S = 1.
 #include <algorithm>
 
 #include "step_common.h"
@@ -258,6 +258,8 @@ __global__ __launch_bounds__(kApFinishBlock) void k_ap_finish(StepArgs a, const 
 // / 38.4 -> 32.4 / 55.6 -> 44.5 / 74.7 -> 57.1 / 115 -> 91; at 12,000 / 32,000
 // FP32 143 -> 102 / 608 -> 545, FP64 284 -> 212 / 1402 -> 1300. FP32 sums get
 // shorter and their error smaller (8,000: 7.6e-7 -> 6.1e-7 of the rms force).
+// The units are this chip's 256 and not the current device's: the splits decide
+// the workspace size, which a host without a device may ask for.
 int allpairs_splits(int64_t n) {
     constexpr int64_t kUnits = 256;
     const int64_t tiles = (n + kWave - 1) / kWave;
