@@ -27,6 +27,7 @@ constexpr int kRowThreads = 256;
 constexpr int kBlockSmall = kRowThreads;  // threads per block of the step kernel for small boxes
 constexpr int kApFinishBlock = 64;  // threads per block of the all-pairs step tail (one wavefront)
 constexpr int kRing = 64;        // steps of block partials kept before an observable flush
+constexpr int kRingLess = 16;    // the same in a workspace that has no room for kRing (see Geom::ring)
 constexpr int kNP = 8;           // doubles per partial row: U, W, K, px, py, pz, -, -
 
 // Latched device error bits (ctl->flags).
@@ -134,7 +135,7 @@ struct State {
     int32_t *rank_of;     // [ncell] Hilbert rank of the cell with linear index (ix*ny+iy)*nz+iz
     int32_t *cell_pos;    // [ncell] grid position of the cell with a given Hilbert rank: ix << 20 | iy << 10 | iz
     uint8_t *scratch;     // resort staging
-    double *partials;     // [kRing][max_blocks][kNP] per-block observable partials
+    double *partials;     // [ring][max_blocks][kNP] per-block observable partials
     int32_t *rebuilt;     // [kRing] 1 if the list was rebuilt before that step's force
     Ctl *ctl;
 };
@@ -150,6 +151,7 @@ struct Geom {
     int32_t ncu;          // compute units of the device (grid of the per-step rebuild kernels)
     int32_t all_pairs;    // 1: untruncated all-pairs interaction (no lists, no cells)
     int32_t dim;          // 2 (motion in the x-y plane, z and v_z held at 0) or 3
+    int32_t ring;         // steps of partials kept (a power of two, at most kRing)
     int32_t nsplit;       // all pairs: splits of the j range (what the workspace holds rows for)
 };
 
@@ -419,6 +421,10 @@ void box_pair_constants(const ljmd_params &p, BoxC &b, PairC &q);
 int check_params_why(const ljmd_params *p, const char **why);
 // Text returned by ljmd_last_error(NULL) (calls without a context).
 void set_global_error(const char *msg);
+// The smallest workspace that ljmd_create and ljmd_batch_create take (0 if the
+// arguments are invalid).
+size_t workspace_least(const ljmd_params *p);
+size_t batch_workspace_least(const ljmd_params *shared, const ljmd_system *sys, int32_t nsys);
 size_t resort_scratch_bytes(int64_t npad, int prec);
 size_t cell_rec_bytes(int prec);
 int step_blocks(const Geom &g);

@@ -168,7 +168,7 @@ __global__ __launch_bounds__(kBlock) void k_obs_reduce(State st, Geom g, int64_t
     const int slot = (int)(step % kRing);
     double acc[6] = {0, 0, 0, 0, 0, 0};
     for (int b = threadIdx.x; b < nblocks; b += kBlock) {
-        const double *r = st.partials + ((size_t)slot * g.max_blocks + b) * kNP;
+        const double *r = st.partials + ((size_t)(slot & (g.ring - 1)) * g.max_blocks + b) * kNP;
         for (int q = 0; q < 6; ++q) acc[q] += r[q];
     }
     for (int q = 0; q < 6; ++q) red[threadIdx.x][q] = acc[q];
@@ -288,7 +288,8 @@ __global__ __launch_bounds__(kBlock) void k_batch_obs(State st, Geom g, const Sy
     double acc[6] = {0, 0, 0, 0, 0, 0};
     constexpr int rows = kBlock / kRowThreads;  // rows of partials per block of the step kernel
     for (int b = threadIdx.x; b < y.nb * rows; b += kBlock) {
-        const double *r = st.partials + ((size_t)slot * g.max_blocks + (size_t)y.b_off * rows + b) * kNP;
+        const double *r =
+            st.partials + ((size_t)(slot & (g.ring - 1)) * g.max_blocks + (size_t)y.b_off * rows + b) * kNP;
         for (int q = 0; q < 6; ++q) acc[q] += r[q];
     }
     for (int q = 0; q < 6; ++q) red[threadIdx.x][q] = acc[q];

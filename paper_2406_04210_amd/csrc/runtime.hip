@@ -248,6 +248,7 @@ struct Plan {
     int ncell;
     int max_blocks;       // rows of partials per step
     int nsplit;           // all pairs: splits of the j range
+    int ring;             // steps of partials kept
     // byte offsets
     size_t off_rec[2], off_vel, off_frc, off_dsw[3], off_img, off_id,
         off_xref, off_nbr, off_cnt, off_ccount, off_cmem, off_cstart, off_rank, off_lin, off_scratch,
@@ -268,6 +269,7 @@ void lay_out(Plan &pl, int prec, int nctl);
 // needs more, the largest that fits (the smallest there is if none does).
 Plan make_plan(const ljmd_params *p, size_t bytes = SIZE_MAX) {
     Plan pl{};
+    pl.ring = kRing;
     pl.npad = (p->n + 63) / 64 * 64;
     grid_dims(p, pl.nc);
     pl.ncell = pl.nc[0] * pl.nc[1] * pl.nc[2];
@@ -320,6 +322,12 @@ Plan make_plan(const ljmd_params *p, size_t bytes = SIZE_MAX) {
     const int per_block = (step_block_threads(p->precision) / kWave) * (kWave / pl.lanes);
     pl.max_blocks = (int)((p->n + per_block - 1) / per_block) * (step_block_threads(p->precision) / kRowThreads);
     lay_out(pl, p->precision, 1);
+    if (pl.total > bytes && step_block_threads(p->precision) > kRowThreads) {
+        // A row per kRowThreads threads for kRingLess steps takes the bytes of a
+        // row per block for kRing steps: a workspace sized for those will do.
+        pl.ring = kRingLess;
+        lay_out(pl, p->precision, 1);
+    }
     return pl;
 }
 
@@ -354,7 +362,7 @@ void lay_out(Plan &pl, int prec, int nctl) {
     pl.off_rank = take(sizeof(int32_t) * pl.ncell);
     pl.off_lin = take(sizeof(int32_t) * pl.ncell);
     pl.off_scratch = take(resort_scratch_bytes(N, prec));
-    pl.off_part = take(sizeof(double) * (size_t)kRing * pl.max_blocks * kNP);
+    pl.off_part = take(sizeof(double) * (size_t)pl.ring * pl.max_blocks * kNP);
     pl.off_rebuilt = take(sizeof(int32_t) * kRing);
     pl.off_ctl = take(sizeof(Ctl) * (size_t)nctl);
     // Lists last, so that a larger workspace is room for longer lists; one
@@ -635,7 +643,7 @@ int step_range(ljmd_ctx *c, int64_t s0, int64_t n, double *obs_dev, const RunOpt
         }
         if (!last) c->cur ^= 1;
         ++pending;
-        if (obs_dev && (pending == kRing || last)) {
+        if (obs_dev && (pending == c->g.ring || last)) {
             Bracket b(c, 3);
             if ((e = launch_obs_reduce(L, first, pending, c->nblocks, obs_dev, row)) != hipSuccess)
                 return hip_fail(c, e, "obs");
@@ -1000,10 +1008,11 @@ struct BatchLayout {
            off_wlcnt = 0, total = 0;
 };
 
-BatchLayout batch_layout(const BatchGeom &bg, int nsys) {
+BatchLayout batch_layout(const BatchGeom &bg, int nsys, int ring = kRing) {
     BatchLayout bl;
     Plan &pl = bl.pl;
     pl = Plan{};
+    pl.ring = ring;
     pl.npad = bg.nslots;
     pl.ncell = (int)bg.ncell;
     pl.cap = bg.cap;
@@ -1067,6 +1076,15 @@ int check_params_why(const ljmd_params *p, const char **why) {
 }
 
 void set_global_error(const char *msg) { g_create_err = msg; }
+
+size_t workspace_least(const ljmd_params *p) {
+    return validate(p, nullptr) == LJMD_OK ? make_plan(p, 0).total : 0;
+}
+
+size_t batch_workspace_least(const ljmd_params *shared, const ljmd_system *sys, int32_t nsys) {
+    BatchGeom bg;
+    return batch_geom(shared, sys, nsys, bg, false) == LJMD_OK ? batch_layout(bg, nsys, kRingLess).total : 0;
+}
 
 }  // namespace ljmd
 
@@ -1140,6 +1158,7 @@ int ljmd_create(const ljmd_params *p, void *ws, size_t bytes, void *stream, ljmd
     g.prec = p->precision;
     g.max_blocks = pl.max_blocks;
     g.all_pairs = all_pairs(p) ? 1 : 0;
+    g.ring = pl.ring;
     g.nsplit = pl.nsplit;
     g.dim = dim_of(p);
     g.ncu = 256;
@@ -1870,6 +1889,7 @@ int ljmd_batch_create(const ljmd_params *shared, const ljmd_system *sys, int32_t
         return r;
     }
     b->bl = batch_layout(b->bg, nsys);
+    if (bytes < b->bl.total) b->bl = batch_layout(b->bg, nsys, kRingLess);  // as for a single box
     if (bytes < b->bl.total) {
         delete b;
         return bfail(nullptr, LJMD_ENOMEM, "workspace has %zu bytes, needs %zu", bytes, b->bl.total);
@@ -1905,6 +1925,7 @@ int ljmd_batch_create(const ljmd_params *shared, const ljmd_system *sys, int32_t
     g.nspecies = 1;
     g.prec = LJMD_FP32_DS;
     g.max_blocks = b->bl.pl.max_blocks;
+    g.ring = b->bl.pl.ring;
     g.dim = 3;
     g.ncu = 256;
     if (b->device >= 0) {

@@ -185,7 +185,7 @@ __device__ inline void block_finish(const StepArgs &a, Ctl *ctl, int blk, double
         double s = 0.0;
         if (c < 6)
             for (int q = 0; q < WPR; ++q) s += red[r * WPR + q][c];
-        a.st.partials[((size_t)a.slot * a.g.max_blocks + (size_t)blk * ROWS) * kNP + threadIdx.x] = s;
+        a.st.partials[((size_t)(a.slot & (a.g.ring - 1)) * a.g.max_blocks + (size_t)blk * ROWS) * kNP + threadIdx.x] = s;
     }
     if (threadIdx.x == 0 && (a.mode & kIntegrate)) {
         uint32_t m = 0;

@@ -111,23 +111,29 @@ int capacity_for(int fill) {
     return cap < 16 ? 16 : (cap > 4096 ? 4096 : cap);
 }
 
+// The largest of size(parameters) over the candidates (0 if it is 0 for any).
+template <class Size>
+size_t candidates_max(const ljmd_params &p, Size size) {
+    size_t best = 0;
+    for (int split : kSplitCandidates)
+        for (int lanes : kLaneCandidates) {
+            ljmd_params q = p;
+            q.lanes = lanes;
+            q.cell_split = split;
+            const size_t s = size(&q);
+            if (s == 0) return 0;
+            best = s > best ? s : best;
+        }
+    return best;
+}
+
 }  // namespace
 
 extern "C" {
 
 size_t ljmd_autotune_workspace_size(const ljmd_params *p) {
     if (ljmd_check_params(p) != LJMD_OK) return 0;
-    size_t best = 0;
-    for (int split : kSplitCandidates)
-        for (int lanes : kLaneCandidates) {
-            ljmd_params q = *p;
-            q.lanes = lanes;
-            q.cell_split = split;
-            const size_t s = ljmd_workspace_size(&q);
-            if (s == 0) return 0;
-            best = s > best ? s : best;
-        }
-    return best;
+    return candidates_max(*p, ljmd_workspace_size);
 }
 
 int ljmd_autotune(const ljmd_params *p, const double *x, const double *v, const int32_t *species, void *ws,
@@ -142,7 +148,7 @@ int ljmd_autotune(const ljmd_params *p, const double *x, const double *v, const 
         out->from_cache = 1;
         return LJMD_OK;
     }
-    if (bytes < ljmd_autotune_workspace_size(p)) return LJMD_ENOMEM;
+    if (bytes < candidates_max(*p, ljmd::workspace_least)) return LJMD_ENOMEM;
     hipStream_t s = (hipStream_t)stream;
     hipEvent_t e0, e1;
     if (hipEventCreate(&e0) != hipSuccess) return LJMD_EHIP;
@@ -193,17 +199,7 @@ int ljmd_autotune(const ljmd_params *p, const double *x, const double *v, const 
 
 size_t ljmd_batch_autotune_workspace_size(const ljmd_params *shared, const ljmd_system *sys, int32_t nsys) {
     if (!shared || !sys || nsys < 1) return 0;
-    size_t best = 0;
-    for (int split : kSplitCandidates)
-        for (int lanes : kLaneCandidates) {
-            ljmd_params q = *shared;
-            q.lanes = lanes;
-            q.cell_split = split;
-            const size_t s = ljmd_batch_workspace_size(&q, sys, nsys);
-            if (s == 0) return 0;
-            best = s > best ? s : best;
-        }
-    return best;
+    return candidates_max(*shared, [&](const ljmd_params *q) { return ljmd_batch_workspace_size(q, sys, nsys); });
 }
 
 int ljmd_batch_autotune(const ljmd_params *shared, const ljmd_system *sys, int32_t nsys, const double *x,
@@ -211,7 +207,8 @@ int ljmd_batch_autotune(const ljmd_params *shared, const ljmd_system *sys, int32
                         int32_t steps, const char *cache_path, ljmd_tuning *out) {
     if (!shared || !sys || nsys < 1 || !x || !v || !species || !ws || !out || steps < 1) return LJMD_EINVAL;
     std::memset(out, 0, sizeof *out);
-    const size_t need = ljmd_batch_autotune_workspace_size(shared, sys, nsys);
+    const size_t need = candidates_max(
+        *shared, [&](const ljmd_params *q) { return ljmd::batch_workspace_least(q, sys, nsys); });
     if (need == 0) return LJMD_EINVAL;
     const std::string key = batch_key(shared, sys, nsys);
     if (cache_path && cache_lookup(cache_path, key, out)) {

@@ -72,3 +72,66 @@ def test_brute_forces_in_less(ljmd, monkeypatch, prec, n, least):
     with pytest.raises(ljmd.LJMDError) as err:
         ljmd.brute_forces(n, w.box, w.params, x, w.species, precision=prec)
     assert err.value.code == -2
+
+
+N = 3000
+
+
+def fluid():
+    return W.thermostat_fluid(N, seed_index=3)
+
+
+@pytest.mark.parametrize("prec,kw,least", [
+    (FP32_DS, {}, 3931136), (FP32_DS, dict(lanes=1), 3918848), (FP32_DS, dict(lanes=16), 4099072),
+    (FP32_DS, dict(nbr_capacity=128), 2391040), (FP32, {}, 3931136)])
+def test_lists_in_less(ljmd, monkeypatch, prec, kw, least):
+    # Fewer steps of partial sums are kept; observables (flushed several times in
+    # 150 steps), state and gradients are the same bit for bit.
+    w = fluid()
+    full = ljmd.workspace_size(ljmd.make_params(N, w.box, w.params, prec, **kw))
+    g = np.random.default_rng(1).standard_normal((N, 3))
+    assert least < full
+    out = []
+    for size in (full, least, full - 256):
+        print(f"lists prec={prec} {kw} workspace {size} of {full}", flush=True)
+        monkeypatch.setattr(ljmd, "workspace_size", lambda p: size)
+        s = ljmd.System(N, w.box, w.params, precision=prec, **kw)
+        s.set_state(w.x, w.v, w.species)
+        obs = s.run(150).cpu().numpy()
+        out.append([obs, s.unwrapped_positions().cpu().numpy(), s.forces().cpu().numpy(),
+                    *(t.cpu().numpy() for t in s.force_vjp(g))])
+    for o in out[1:]:
+        for a, b in zip(out[0], o):
+            assert np.array_equal(a, b)
+    monkeypatch.setattr(ljmd, "workspace_size", lambda p: least - 256)
+    with pytest.raises(ljmd.LJMDError) as err:
+        ljmd.System(N, w.box, w.params, precision=prec, **kw)
+    assert err.value.code == -2
+
+
+def test_batch_and_tuner_in_less(ljmd, monkeypatch):
+    sizes = [500, 700, 1000, 3000]
+    ws = [W.thermostat_fluid(n, seed_index=3) for n in sizes]
+    edges = [(n / 0.8442) ** (1.0 / 3.0) for n in sizes]
+    x, v = np.concatenate([w.x for w in ws]), np.concatenate([w.v for w in ws])
+    sp = np.concatenate([w.species for w in ws])
+    out = []
+    for size in (None, 4656640):
+        if size:
+            monkeypatch.setattr(ljmd.lib, "ljmd_batch_workspace_size", lambda *a: size)
+        b = ljmd.Batch(sizes, edges, ws[0].params)
+        b.set_state(x, v, sp)
+        obs = [b.run(k, observe=True).cpu().numpy() for k in (1, 30, 17, 70)]
+        out.append([*obs, b.forces().cpu().numpy()])
+    for a, c in zip(*out):
+        assert np.array_equal(a, c)
+    monkeypatch.setattr(ljmd.lib, "ljmd_batch_workspace_size", lambda *a: 4656640 - 256)
+    with pytest.raises(ljmd.LJMDError) as err:
+        ljmd.Batch(sizes, edges, ws[0].params)
+    assert err.value.code == -2
+    monkeypatch.undo()
+    monkeypatch.setattr(ljmd.lib, "ljmd_batch_autotune_workspace_size", lambda *a: 5634560)
+    monkeypatch.setattr(ljmd.lib, "ljmd_autotune_workspace_size", lambda *a: 4593408)
+    assert ljmd.autotune_batch(sizes, edges, ws[0].params, x, v, sp, steps=5)["lanes"] in (1, 2, 4, 8, 16)
+    w = fluid()
+    assert ljmd.autotune(N, w.box, w.params, w.x, w.v, w.species, steps=5)["lanes"] in (1, 2, 4, 8, 16)
