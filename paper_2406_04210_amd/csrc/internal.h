@@ -27,7 +27,7 @@ constexpr int kRowThreads = 256;
 constexpr int kBlockSmall = kRowThreads;  // threads per block of the step kernel for small boxes
 constexpr int kApFinishBlock = 64;  // threads per block of the all-pairs step tail (one wavefront)
 constexpr int kRing = 64;        // steps of block partials kept before an observable flush
-constexpr int kRingLess = 16;    // the same in a workspace that has no room for kRing (see Geom::ring)
+constexpr int kRingLess = 16;    // the same in a workspace that has no room for kRing (a divisor of kRing)
 constexpr int kNP = 8;           // doubles per partial row: U, W, K, px, py, pz, -, -
 
 // Latched device error bits (ctl->flags).
@@ -151,7 +151,6 @@ struct Geom {
     int32_t ncu;          // compute units of the device (grid of the per-step rebuild kernels)
     int32_t all_pairs;    // 1: untruncated all-pairs interaction (no lists, no cells)
     int32_t dim;          // 2 (motion in the x-y plane, z and v_z held at 0) or 3
-    int32_t ring;         // steps of partials kept (a power of two, at most kRing)
     int32_t nsplit;       // all pairs: splits of the j range (what the workspace holds rows for)
 };
 
@@ -389,9 +388,10 @@ enum : int { kFinalize = 1, kIntegrate = 2, kStoreForce = 4, kObserve = 8 };
 // Particle slots below which the quanta force loop addresses records by a
 // 32-bit byte offset.
 constexpr int64_t kQuantaMaxSlots = (int64_t)1 << 28;
+// slot: of the partials, the step modulo the steps kept.
 hipError_t launch_step(const Launch &L, int64_t step, int forced, int mode, int slot);
 hipError_t launch_integrate(const Launch &L, int64_t step);
-hipError_t launch_obs_reduce(const Launch &L, int64_t first_step, int count, int nblocks,
+hipError_t launch_obs_reduce(const Launch &L, int64_t first_step, int count, int nblocks, int ring,
                              double *obs_dev, int64_t obs_row0);
 hipError_t launch_get_state(const Launch &L, double *x, double *v, int32_t *img);
 hipError_t launch_get_forces(const Launch &L, double *f);

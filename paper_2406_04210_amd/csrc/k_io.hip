@@ -160,15 +160,15 @@ __global__ __launch_bounds__(kBlock) void k_neighbors(State st, Geom g, int32_t 
 // order (strided per thread, then a fixed LDS tree), so the FP64 sums are
 // bit-reproducible. Row layout out: U, K, W, px, py, pz, rebuilt, step.
 __global__ __launch_bounds__(kBlock) void k_obs_reduce(State st, Geom g, int64_t first_step,
-                                                       int nblocks, double *obs, int64_t row0,
+                                                       int nblocks, int ring, double *obs, int64_t row0,
                                                        int count) {
     __shared__ double red[kBlock][6];
     const int sidx = blockIdx.x;
     const int64_t step = first_step + sidx;
-    const int slot = (int)(step % kRing);
+    const int slot = (int)(step % ring);
     double acc[6] = {0, 0, 0, 0, 0, 0};
     for (int b = threadIdx.x; b < nblocks; b += kBlock) {
-        const double *r = st.partials + ((size_t)(slot & (g.ring - 1)) * g.max_blocks + b) * kNP;
+        const double *r = st.partials + ((size_t)slot * g.max_blocks + b) * kNP;
         for (int q = 0; q < 6; ++q) acc[q] += r[q];
     }
     for (int q = 0; q < 6; ++q) red[threadIdx.x][q] = acc[q];
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(kBlock) void k_obs_reduce(State st, Geom g, int64_t
     }
     if (threadIdx.x == 0) {
         double row[kNP] = {red[0][0], red[0][2], red[0][1], red[0][3],
-                           red[0][4], red[0][5], (double)st.rebuilt[slot], (double)step};
+                           red[0][4], red[0][5], (double)st.rebuilt[step % kRing], (double)step};
         if (obs)
             for (int q = 0; q < kNP; ++q) obs[(row0 + sidx) * kNP + q] = row[q];
         if (sidx == count - 1)
@@ -288,8 +288,7 @@ __global__ __launch_bounds__(kBlock) void k_batch_obs(State st, Geom g, const Sy
     double acc[6] = {0, 0, 0, 0, 0, 0};
     constexpr int rows = kBlock / kRowThreads;  // rows of partials per block of the step kernel
     for (int b = threadIdx.x; b < y.nb * rows; b += kBlock) {
-        const double *r =
-            st.partials + ((size_t)(slot & (g.ring - 1)) * g.max_blocks + (size_t)y.b_off * rows + b) * kNP;
+        const double *r = st.partials + ((size_t)slot * g.max_blocks + (size_t)y.b_off * rows + b) * kNP;
         for (int q = 0; q < 6; ++q) acc[q] += r[q];
     }
     for (int q = 0; q < 6; ++q) red[threadIdx.x][q] = acc[q];
@@ -359,11 +358,11 @@ hipError_t launch_neighbors(const Launch &L, int32_t *cnt, int32_t *ids, int32_t
     return hipGetLastError();
 }
 
-hipError_t launch_obs_reduce(const Launch &L, int64_t first_step, int count, int nblocks,
+hipError_t launch_obs_reduce(const Launch &L, int64_t first_step, int count, int nblocks, int ring,
                              double *obs_dev, int64_t obs_row0) {
     if (count <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_obs_reduce, dim3(count), dim3(kBlock), 0, L.stream, *L.st, *L.g,
-                       first_step, nblocks, obs_dev, obs_row0, count);
+                       first_step, nblocks, ring, obs_dev, obs_row0, count);
     return hipGetLastError();
 }
 

@@ -268,7 +268,7 @@ hipError_t launch_sd(const Launch &L, int64_t step, int forced, int iter, double
     sa.s.cur = L.cur;
     sa.s.forced = forced;
     sa.s.mode = 0;
-    sa.s.slot = (int)(step % kRing);
+    sa.s.slot = 0;  // no partials
     sa.s.step = step;
     for (int t = 0; t < 3; ++t) {
         const double c2 = clamp * clamp * L.pc->sig2[t];

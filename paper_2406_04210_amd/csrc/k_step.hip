@@ -409,7 +409,7 @@ template <int NS, int LANES, bool Q, bool OBS, bool TH, bool PLAIN>
 __global__ __launch_bounds__(kBlock) void k_step_ds(StepArgs a) {
     static_assert(OBS || Q, "observables are skipped on the quanta path only");
     step_ds_body<NS, LANES, Q, OBS, TH, PLAIN>(a, a.box, a.st.ctl, xcd_remap(blockIdx.x, gridDim.x), a.g.n, 0,
-                                               a.box.ncell, blockIdx.x, gridDim.x, a.st.rebuilt + a.slot);
+                                               a.box.ncell, blockIdx.x, gridDim.x, rebuilt_mark(a));
 }
 // Two species, NVE: held to 64 VGPRs, eight waves per SIMD (unbounded it
 // takes 65-66 and drops to seven; the 4M mixture's step kernel measured
@@ -418,7 +418,7 @@ template <int LANES, bool Q, bool OBS, bool PLAIN>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) void k_step_ds_mix(StepArgs a) {
     static_assert(OBS || Q, "observables are skipped on the quanta path only");
     step_ds_body<2, LANES, Q, OBS, false, PLAIN>(a, a.box, a.st.ctl, xcd_remap(blockIdx.x, gridDim.x), a.g.n, 0,
-                                                 a.box.ncell, blockIdx.x, gridDim.x, a.st.rebuilt + a.slot);
+                                                 a.box.ncell, blockIdx.x, gridDim.x, rebuilt_mark(a));
 }
 template <int NS, int LANES, bool Q, bool OBS, bool TH, bool PLAIN>
 constexpr void (*step_ds_kernel())(StepArgs) {
@@ -437,7 +437,7 @@ template <int NS, bool OBS, bool TH, bool PLAIN>
 __global__ __launch_bounds__(kBlockSmall) void k_step_ds_small(StepArgs a) {
     step_ds_body<NS, 2, true, OBS, TH, PLAIN, kBlockSmall, true>(a, a.box, a.st.ctl, xcd_remap(blockIdx.x, gridDim.x),
                                                                  a.g.n, 0, a.box.ncell, blockIdx.x, gridDim.x,
-                                                                 a.st.rebuilt + a.slot);
+                                                                 rebuilt_mark(a));
 }
 
 // The form for large boxes in blocks of 256 threads (see fine_blocks); eight
@@ -446,7 +446,7 @@ template <int NS, bool OBS, bool TH, bool PLAIN>
 __global__ __launch_bounds__(kBlockSmall, (TH ? 4 : 8)) void k_step_ds_fine(StepArgs a) {
     step_ds_body<NS, 2, true, OBS, TH, PLAIN, kBlockSmall>(a, a.box, a.st.ctl, xcd_remap(blockIdx.x, gridDim.x), a.g.n,
                                                            0, a.box.ncell, blockIdx.x, gridDim.x,
-                                                           a.st.rebuilt + a.slot);
+                                                           rebuilt_mark(a));
 }
 
 // A batch of independent one-species cubic systems, each over its own run of
@@ -533,7 +533,7 @@ __device__ inline void step_fp64_body(const StepArgs &a) {
         cnt = valid ? (int)c : 0;
     }
     if (halted_record(a.st.ctl, a.step, blockIdx.x == 0)) return;
-    step_housekeeping(a, a.st.ctl, 0, a.box.ncell, blockIdx.x, gridDim.x, a.st.rebuilt + a.slot);
+    step_housekeeping(a, a.st.ctl, 0, a.box.ncell, blockIdx.x, gridDim.x, rebuilt_mark(a));
     if constexpr (!SMALL) {
         if (valid) {
             ri = rec[i];

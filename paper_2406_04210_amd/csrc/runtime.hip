@@ -102,6 +102,7 @@ struct ljmd_ctx {
     int64_t step = 0;
     bool have_state = false;
     int nblocks = 0;
+    int ring = kRing;  // steps of observable partials the workspace holds
     std::string err;
     // Kernel timing (ljmd_set_profiling): event pairs per family, resolved lazily.
     bool profiling = false;
@@ -637,15 +638,15 @@ int step_range(ljmd_ctx *c, int64_t s0, int64_t n, double *obs_dev, const RunOpt
             Bracket b(c, 0, !c->g.all_pairs);
             L.ev0 = b.ev(0);
             L.ev1 = b.ev(1);
-            e = launch_step(L, s, forced, mode, (int)(s % kRing));
+            e = launch_step(L, s, forced, mode, (int)(s % c->ring));
             L.ev0 = L.ev1 = nullptr;
             if (e != hipSuccess) return hip_fail(c, e, "step");
         }
         if (!last) c->cur ^= 1;
         ++pending;
-        if (obs_dev && (pending == c->g.ring || last)) {
+        if (obs_dev && (pending == c->ring || last)) {
             Bracket b(c, 3);
-            if ((e = launch_obs_reduce(L, first, pending, c->nblocks, obs_dev, row)) != hipSuccess)
+            if ((e = launch_obs_reduce(L, first, pending, c->nblocks, c->ring, obs_dev, row)) != hipSuccess)
                 return hip_fail(c, e, "obs");
             row += pending;
             first += pending;
@@ -654,7 +655,7 @@ int step_range(ljmd_ctx *c, int64_t s0, int64_t n, double *obs_dev, const RunOpt
     }
     if (!obs_dev && o.final_obs) {
         Bracket b(c, 3);
-        if ((e = launch_obs_reduce(L, s0 + n - 1, 1, c->nblocks, nullptr, 0)) != hipSuccess)
+        if ((e = launch_obs_reduce(L, s0 + n - 1, 1, c->nblocks, c->ring, nullptr, 0)) != hipSuccess)
             return hip_fail(c, e, "obs");
     }
     c->step = s0 + n - 1;
@@ -1158,7 +1159,7 @@ int ljmd_create(const ljmd_params *p, void *ws, size_t bytes, void *stream, ljmd
     g.prec = p->precision;
     g.max_blocks = pl.max_blocks;
     g.all_pairs = all_pairs(p) ? 1 : 0;
-    g.ring = pl.ring;
+    c->ring = pl.ring;
     g.nsplit = pl.nsplit;
     g.dim = dim_of(p);
     g.ncu = 256;
@@ -1223,7 +1224,7 @@ int ljmd_set_state(ljmd_ctx *c, const double *x, const double *v, const int32_t 
     for (;;) {
         L = launcher(c);
         if ((e = launch_step(L, 0, 1, kStoreForce | kObserve, 0)) != hipSuccess) return hip_fail(c, e, "force");
-        if ((e = launch_obs_reduce(L, 0, 1, c->nblocks, nullptr, 0)) != hipSuccess)
+        if ((e = launch_obs_reduce(L, 0, 1, c->nblocks, c->ring, nullptr, 0)) != hipSuccess)
             return hip_fail(c, e, "obs");
         // A list overflow of the first build: grow the lists and build again
         // (the positions stay where the state load put them).
@@ -1331,9 +1332,9 @@ int ljmd_minimize_sd(ljmd_ctx *c, int32_t nsteps, double max_disp, double clamp,
         int r = rebuild_sequence(c, c->step, 1, true);
         if (r) return r;
         Launch L = launcher(c);
-        if ((e = launch_step(L, c->step, 1, kStoreForce | kObserve, (int)(c->step % kRing))) != hipSuccess)
+        if ((e = launch_step(L, c->step, 1, kStoreForce | kObserve, (int)(c->step % c->ring))) != hipSuccess)
             return hip_fail(c, e, "force");
-        if ((e = launch_obs_reduce(L, c->step, 1, c->nblocks, nullptr, 0)) != hipSuccess)
+        if ((e = launch_obs_reduce(L, c->step, 1, c->nblocks, c->ring, nullptr, 0)) != hipSuccess)
             return hip_fail(c, e, "obs");
         Ctl h;
         bool redo = false;
@@ -1436,9 +1437,9 @@ int ljmd_set_pair_params(ljmd_ctx *c, const double eps[4], const double sigma[4]
     // Forces and observables of the current positions under the new values.
     Launch L = launcher(c);
     hipError_t e;
-    if ((e = launch_step(L, c->step, 0, kStoreForce | kObserve, (int)(c->step % kRing))) != hipSuccess)
+    if ((e = launch_step(L, c->step, 0, kStoreForce | kObserve, (int)(c->step % c->ring))) != hipSuccess)
         return hip_fail(c, e, "force");
-    if ((e = launch_obs_reduce(L, c->step, 1, c->nblocks, nullptr, 0)) != hipSuccess)
+    if ((e = launch_obs_reduce(L, c->step, 1, c->nblocks, c->ring, nullptr, 0)) != hipSuccess)
         return hip_fail(c, e, "obs");
     return LJMD_OK;
 }
@@ -1809,7 +1810,7 @@ int batch_one_step(ljmd_batch *b, int64_t s, bool last) {
     if (r) return r;
     Launch L = blauncher(b);
     hipError_t e = launch_batch_step(L, b->sys, b->g16, b->bg.nblocks, s, forced,
-                                     kFinalize | (last ? kStoreForce | kObserve : kIntegrate), (int)(s % kRing));
+                                     kFinalize | (last ? kStoreForce | kObserve : kIntegrate), (int)(s % b->bl.pl.ring));
     if (e != hipSuccess) return bhip(b, e, "batch step");
     if (!last) b->cur ^= 1;
     return LJMD_OK;
@@ -1925,7 +1926,6 @@ int ljmd_batch_create(const ljmd_params *shared, const ljmd_system *sys, int32_t
     g.nspecies = 1;
     g.prec = LJMD_FP32_DS;
     g.max_blocks = b->bl.pl.max_blocks;
-    g.ring = b->bl.pl.ring;
     g.dim = 3;
     g.ncu = 256;
     if (b->device >= 0) {
@@ -2051,7 +2051,7 @@ int ljmd_batch_run(ljmd_batch *b, int64_t nsteps, double *obs_dev) {
     }
     L = blauncher(b);
     b->step += nsteps;
-    if ((e = launch_batch_obs(L, b->sys, b->nsys, (int)(b->step % kRing), b->step, obs_dev)) != hipSuccess)
+    if ((e = launch_batch_obs(L, b->sys, b->nsys, (int)(b->step % b->bl.pl.ring), b->step, obs_dev)) != hipSuccess)
         return bhip(b, e, "batch obs");
     return LJMD_OK;
 }

@@ -16,9 +16,12 @@ struct StepArgs {
     int cur;
     int forced;
     int mode;
-    int slot;
+    int slot;  // of the partials
     int64_t step;
 };
+
+// The rebuild marker of the step.
+__device__ inline int32_t *rebuilt_mark(const StepArgs &a) { return a.st.rebuilt + (a.step & (kRing - 1)); }
 
 template <int NS, class T>
 __device__ inline T by_t(int t, const T (&a)[3]) {
@@ -185,7 +188,7 @@ __device__ inline void block_finish(const StepArgs &a, Ctl *ctl, int blk, double
         double s = 0.0;
         if (c < 6)
             for (int q = 0; q < WPR; ++q) s += red[r * WPR + q][c];
-        a.st.partials[((size_t)(a.slot & (a.g.ring - 1)) * a.g.max_blocks + (size_t)blk * ROWS) * kNP + threadIdx.x] = s;
+        a.st.partials[((size_t)a.slot * a.g.max_blocks + (size_t)blk * ROWS) * kNP + threadIdx.x] = s;
     }
     if (threadIdx.x == 0 && (a.mode & kIntegrate)) {
         uint32_t m = 0;
