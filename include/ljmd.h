@@ -147,7 +147,8 @@ int ljmd_check_params(const ljmd_params *p);
  * ljmd_create also takes less in the single-precision paths: a quarter of the
  * steps of observable partials (16 instead of 64 between two reductions),
  * 12,288 bytes less per 1,024 lanes of the force gather (n * lanes, rounded up;
- * two lanes by default). Results are the same.
+ * two lanes by default), and lays itself out so where that lets lists grow
+ * further. Results are the same.
  *
  * The untruncated all-pairs interaction (every used rcut = +inf: the
  * interaction of the paper's all-to-all study, Sec. 4 and Sec. 5 "GPU

@@ -262,6 +262,14 @@ inline size_t al(size_t b) { return (b + 255) & ~(size_t)255; }
 // Bytes of the neighbour lists of npad slots with cap entries each.
 inline size_t list_bytes(int64_t npad, int32_t cap) { return sizeof(int32_t) * ((size_t)npad * cap + kListPad); }
 
+// Largest list capacity of a workspace of `bytes` whose lists start at off_nbr.
+int32_t list_room(size_t bytes, size_t off_nbr, int64_t npad, int32_t lanes) {
+    if (bytes <= off_nbr + list_bytes(npad, 0)) return 0;
+    const int64_t slots = (int64_t)((bytes - off_nbr - list_bytes(npad, 0)) / sizeof(int32_t) / (size_t)npad);
+    const int32_t gr = cap_granule(lanes);
+    return (int32_t)std::min<int64_t>(4096, slots / gr * gr);
+}
+
 int32_t round_up(int32_t v, int32_t m) { return (v + m - 1) / m * m; }
 
 void lay_out(Plan &pl, int prec, int nctl);
@@ -323,11 +331,16 @@ Plan make_plan(const ljmd_params *p, size_t bytes = SIZE_MAX) {
     const int per_block = (step_block_threads(p->precision) / kWave) * (kWave / pl.lanes);
     pl.max_blocks = (int)((p->n + per_block - 1) / per_block) * (step_block_threads(p->precision) / kRowThreads);
     lay_out(pl, p->precision, 1);
-    if (pl.total > bytes && step_block_threads(p->precision) > kRowThreads) {
+    if (bytes != SIZE_MAX && step_block_threads(p->precision) > kRowThreads) {
         // A row per kRowThreads threads for kRingLess steps takes the bytes of a
-        // row per block for kRing steps: a workspace sized for those will do.
-        pl.ring = kRingLess;
-        lay_out(pl, p->precision, 1);
+        // row per block for kRing steps: a workspace sized for those will do, and
+        // has the room for lists to grow that its size was chosen for.
+        Plan less = pl;
+        less.ring = kRingLess;
+        lay_out(less, p->precision, 1);
+        if (pl.total > bytes ||
+            list_room(bytes, less.off_nbr, pl.npad, pl.lanes) > list_room(bytes, pl.off_nbr, pl.npad, pl.lanes))
+            pl = less;
     }
     return pl;
 }
@@ -725,14 +738,7 @@ int flags_status(ljmd_ctx *c, uint32_t flags) {
 }
 
 // Largest list capacity the workspace holds.
-int32_t cap_limit(const ljmd_ctx *c) {
-    const size_t room = c->ws_bytes - c->off_nbr;
-    const size_t pad = sizeof(int32_t) * kListPad;
-    if (room <= pad) return 0;
-    const int64_t slots = (int64_t)((room - pad) / sizeof(int32_t) / (size_t)c->npad);
-    const int32_t gr = cap_granule(c->g.lanes);
-    return (int32_t)std::min<int64_t>(4096, slots / gr * gr);
-}
+int32_t cap_limit(const ljmd_ctx *c) { return list_room(c->ws_bytes, c->off_nbr, c->npad, c->g.lanes); }
 
 // After a list overflow (lists of `need` entries): a larger capacity within
 // the workspace, the list area cleared to valid indices, the error and halt

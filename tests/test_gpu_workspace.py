@@ -109,6 +109,20 @@ def test_lists_in_less(ljmd, monkeypatch, prec, kw, least):
     assert err.value.code == -2
 
 
+def test_lists_grow_to_what_the_workspace_was_sized_for(ljmd, monkeypatch):
+    # The bytes of lists of 96 entries, opened with a capacity of 32: lists of 81
+    # to 96 entries find their room.
+    w = fluid()
+    ref = ljmd.System(N, w.box, w.params, precision=FP32_DS)
+    ref.set_state(w.x, w.v, w.species)
+    obs = ref.run(100).cpu().numpy()
+    monkeypatch.setattr(ljmd, "workspace_size", lambda p: 2006016)
+    s = ljmd.System(N, w.box, w.params, precision=FP32_DS, nbr_capacity=32)
+    s.set_state(w.x, w.v, w.species)
+    assert np.array_equal(s.run(100).cpu().numpy()[:, :6], obs[:, :6])
+    assert 80 < s.observables()["nbr_capacity"] <= 96
+
+
 def test_batch_and_tuner_in_less(ljmd, monkeypatch):
     sizes = [500, 700, 1000, 3000]
     ws = [W.thermostat_fluid(n, seed_index=3) for n in sizes]
