@@ -35,8 +35,8 @@ HBM_PEAK_GBS = 8000.0
 # 512 MiB copy reads), valid only for the kernel sources they were taken on.
 STEP_KERNEL_SOURCES = ("k_step.hip", "step_common.h", "internal.h")
 STEP_KERNEL_TRAFFIC = {
-    "sources_sha256": "f987689dd5264eecc0d8f829c18b0029e9f29f7464ca65f05bea6ebf2a6c71ef",
-    "fetch_bytes": 2.0 * 53431 * 1024,
+    "sources_sha256": "d2cdd536fc0ce2690c8fb49aada6d6539cc2a64071e4ad9db249b7ca9009875e",
+    "fetch_bytes": 2.0 * 53436 * 1024,
     "write_bytes": 1.0 * 16128 * 1024,
 }
 
