@@ -594,10 +594,11 @@ __device__ inline void nlist_homes_queued(const State &st, const Geom &g, const 
 // a second, cheap test per candidate. rec: the particles' position records,
 // the same as the cell slots hold.
 //
-// What bounds it (FP32, N = 256,000, 80 us per rebuild): the home particles'
-// exact tests take 50 us of it, the list stores 4 us; of the tests' vector
-// instructions the conversions, compares and bit counts run at half rate
-// (1.7 ns per wave against 1.0 ns for an integer or float add or multiply).
+// What bounds it (FP32, N = 256,000, 76 to 78 us per rebuild; shares taken at
+// 80): the home particles' exact tests take 50 us of it, the list stores 4 us;
+// of the tests' vector instructions the conversions, compares and bit counts
+// run at half rate (1.7 ns per wave against 1.0 ns for an integer or float add
+// or multiply).
 // FP64 (N = 256,000): 200 us per rebuild with every candidate tested exactly,
 // 120 us with the reduction.
 // LG: log2 of the lanes per particle of the list layout when it is known at
@@ -886,7 +887,7 @@ __device__ inline void nlist_cell(const State &st, const Geom &g, const BoxC &bo
 
 // Waves per SIMD the list build's registers are held to. One species: six
 // (80 registers). Two species: five without spills; six spill, and large boxes
-// (the per-XCD queues) run five waves anyway: 1.30 against 1.33 ms per rebuild
+// (the per-XCD queues) run five waves anyway: 1.39 against 1.41 ms per rebuild
 // of the 4M mixture. FP64: four (96-100 registers). One species going on from
 // cell to cell (LOOP) spills at six.
 template <int PREC, int NS, bool LOOP>
