@@ -131,3 +131,26 @@ def test_fp64_lists_with_and_without_the_reduction(ljmd, n, cells):
     s = ljmd.System(n, box, p, precision=FP64)
     s.set_state(x, v, sp)
     check_lists(s, x, sp, box, p, FP64)
+
+
+@pytest.mark.parametrize("prec", [FP64, FP32_DS])
+@pytest.mark.parametrize("cells,kw", [((55, 40, 61), {}), ((45, 45, 45), dict(lanes=4)), ((45, 45, 45), dict(lanes=16)),
+                                      ((24, 24, 24), dict(cell_split=2)), ((21, 30, 24), dict(cell_split=2, lanes=1))])
+def test_dilute_lists_of_other_layouts(ljmd, prec, cells, kw):
+    # The striding grid in boxes that are not cubic, at other numbers of lanes,
+    # and over half-size cells with the 125-cell stencil.
+    n = 14000
+    edges = 2.8 * 1.001 * np.array(cells)
+    x, v = gas(n, edges.min(), 3, sum(cells))
+    x *= edges / edges.min()  # stretched: the nearest pairs are no closer
+    p = W.single_species_params()
+    sp = np.zeros(n, dtype=np.int32)
+    s = ljmd.System(n, edges, p, precision=prec, **kw)
+    k = kw.get("cell_split", 1)
+    grid = ljmd.cell_grid(s.params)
+    assert all(k * c <= g <= k * (c + 1) for c, g in zip(cells, grid)) and np.prod(grid) > 12288
+    s.set_state(x, v, sp)
+    check_lists(s, x, sp, edges, p, prec)
+    obs = s.run(15).cpu().numpy()
+    s.sync()
+    assert np.isfinite(obs).all()
